@@ -26,6 +26,16 @@
 // node once for T steps; the price is the redundant work on the tile's rim
 // and on the T planes of z halo at each end of a chunk.
 //
+// A level's rows are computed in straight-line code, stage by stage, and its
+// tallies follow in a branch of their own; planes that no output of the chunk
+// depends on are skipped (T (T + 1) of a chunk's T (zc + 2 T) level-planes).
+// Against per-row branches, global addresses in vector registers and edge rows
+// of one species per access: 184.8 us instead of 189 per step on the
+// 512 x 512 x 256 grid, 39.7 instead of 40.2 on 256 x 256 x 200 (T = 3, R = 4).
+// What bounds the pass is FP64 issue (23 FP64 instructions and 8 lane shifts per
+// node, level and both species, about 1.5 of them per owned node with the rims)
+// at 75 % of the issue slots when nothing waits on HBM, and HBM beside it.
+//
 // The per-step tallies (the same quantities as the one-step kernel, one
 // record per level) are taken on owned columns and on the block's own chunk
 // of planes only, so every node and electrode face is counted once.
@@ -39,7 +49,29 @@ constexpr int kBW = 8;                // waves per block
 constexpr int kBX = 64;               // columns of the extended tile
 constexpr int kBNT = kBW * kWave;     // threads per block
 
-typedef __attribute__((address_space(1))) double gdouble;
+// A plane as a buffer resource: its base and size in scalar registers, so a
+// node costs one 32-bit offset register, and an access beyond the plane reads
+// zero or stores nothing.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
+
+__device__ inline rsrc_t plane_rsrc(const void* plane, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(__attribute__((address_space(1))) void*)uniform_ptr(plane), 0, bytes,
+                                           0x00027000);
+}
+
+__device__ inline double load_b64(rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+
+__device__ inline void store_b64(rsrc_t r, unsigned off, double v) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2_t, v), r, off, 0, 0);
+}
+
+__device__ inline void store_b64_nt(rsrc_t r, unsigned off, double v) {
+  constexpr int kNonTemporal = 2;
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2_t, v), r, off, 0, kNonTemporal);
+}
 
 // Block b of a blocked launch of 8 per_xcd blocks -> its entry in the tile
 // list.  A blocked block fills a CU, so a launch runs in rounds of 256
@@ -94,8 +126,9 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
   constexpr int OX = kBX - 2 * T, OY = EY - 2 * T;
   constexpr int NE = SC ? 7 : 5;          // index of the escaped tallies (AB)
   constexpr int NA = NE + (AB ? 2 : 0);   // tallies kept per level
-  // edge rows of each level's newest plane: [buffer][level][wave][first/last][species][lane]
-  __shared__ double edge_rows[2][T][kBW][2][2][kWave];
+  // edge rows of each level's newest plane, both species of a node together
+  // (16-byte accesses): [buffer][level][wave][first/last][lane]
+  __shared__ double2_t edge_rows[2][T][kBW][2][kWave];
   __shared__ double edge_sum[T][kBW][4];  // per-wave sums of n on the planes next to the electrodes
   __shared__ double lds[(kBNT / kWave) * kAcc * T];
 
@@ -109,6 +142,7 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
   const bool own_x = lane >= T && lane < kBX - T && x0 + (lane - T) < nx;
   unsigned off[R];  // in-plane byte offsets of the thread's nodes
   bool own_y[R];    // the row is owned (wave-uniform)
+  bool all_own = true;
   // absorbing: the node lies in the cell (else it holds zero), and the
   // missing neighbours of the lane's column and of each row
   const bool absorbing = AB && p.absorbing;
@@ -124,6 +158,7 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
     if (ys < 0) ys += ny;
     off[r] = (unsigned)(ys * nx + xs) * 8u;
     own_y[r] = tc.valid && g >= T && g < EY - T && y0 + (g - T) < ny;
+    all_own = all_own && own_y[r];
     const int gy = y0 - T + g;
     in_y[r] = !absorbing || (gy >= 0 && gy < ny);
     miss_y[r] = absorbing ? (double)((gy == 0) + (gy == ny - 1)) : 0.0;
@@ -131,6 +166,7 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
   const int za = 1 + tc.zc * p.zc;
   const int zb = tc.valid ? min(za + p.zc, nz) : za;
   const size_t plane = (size_t)nx * ny;
+  const unsigned plane_bytes = (unsigned)plane * 8u;  // at most 2^31 (checked on the host)
   const Coef cp = p.cp, cn = p.cn;
   const double beta = p.beta, gsp = p.gsp, gsn = p.gsn;
   double add_max = 0.0;  // largest owned output density after a pulse is added
@@ -168,29 +204,29 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
   double pa[R], na[R], pb[R], nb[R];
   auto load0 = [&](int K, double (&lp)[R], double (&ln)[R]) {
     const int Kc = min(max(K, 0), nz);
-    const gchar* bp = uniform_ptr(p.pin + (size_t)Kc * plane);
-    const gchar* bn = uniform_ptr(p.nin + (size_t)Kc * plane);
+    const rsrc_t bp = plane_rsrc(p.pin + (size_t)Kc * plane, plane_bytes);
+    const rsrc_t bn = plane_rsrc(p.nin + (size_t)Kc * plane, plane_bytes);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      lp[r] = *(const gdouble*)(bp + off[r]);
-      ln[r] = *(const gdouble*)(bn + off[r]);
+      lp[r] = load_b64(bp, off[r]);
+      ln[r] = load_b64(bn, off[r]);
       if (AB && !(in_x && in_y[r])) lp[r] = ln[r] = 0.0;  // beyond an absorbing boundary
     }
   };
   // the zero planes' edge rows held at the start
 #pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      edge_rows[Klo & 1][t][w][0][s][lane] = 0.0;
-      edge_rows[Klo & 1][t][w][1][s][lane] = 0.0;
-    }
+  for (int t = 0; t < T; ++t) {
+    edge_rows[Klo & 1][t][w][0][lane] = double2_t{0.0, 0.0};
+    edge_rows[Klo & 1][t][w][1][lane] = double2_t{0.0, 0.0};
+  }
   const int wu = w > 0 ? w - 1 : 0, wd = w < kBW - 1 ? w + 1 : kBW - 1;
 
   // One iteration: planes K - t of levels t = 1..T, then the edge rows of
   // every level's newest plane for the next iteration; level 0 of plane K
   // comes from (lp, ln), which then take the plane kAhead further (with two
   // buffers, past the chunk's last plane a clamped plane, unused).
+  // The update of a level's rows is straight-line code, so that the compiler
+  // interleaves their chains; the tallies follow in a branch of their own.
   auto iterate = [&](int K, double (&lp)[R], double (&ln)[R]) {
     const int buf = K & 1;
     lds_barrier();  // the edge rows written at the end of the previous iteration
@@ -200,11 +236,22 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
       vp[r] = lp[r];
       vn[r] = ln[r];
     }
+    // neighbours above the strip's first row and below its last, level t-1 on
+    // plane K - t (the other waves' edge rows): requested one level ahead
+    double2_t up = edge_rows[buf][0][wu][1][lane], dn = edge_rows[buf][0][wd][0][lane];
     if (kTwoBuffers || K + 1 <= Khi) load0(K + kAhead, lp, ln);
 #pragma unroll
     for (int t = 1; t <= T; ++t) {
+      const double2_t up_t = up, dn_t = dn;
+      if (t < T) {
+        up = edge_rows[buf][t][wu][1][lane];
+        dn = edge_rows[buf][t][wd][0][lane];
+      }
+      __builtin_amdgcn_sched_barrier(0);
       const int q = K - t;  // plane of level t in this iteration (block-uniform)
-      const bool interior = q >= 1 && q <= nz - 1;
+      // planes this level has to have: those the chunk's last level depends
+      // on, electrode planes and beyond hold zero (block-uniform)
+      const bool wanted = q >= max(1, za - T + t) && q <= nz - 1;
       const bool counted = q >= za && q < zb;
       if (counted && (q == 1 || q == nz - 1)) {  // the old values of step t next to an electrode
         double sp_ = 0.0, sn_ = 0.0;
@@ -227,58 +274,101 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
           }
         }
       }
-      // neighbours above the strip's first row and below its last, level t-1
-      // on plane q (the other waves' edge rows)
-      const double up_p = edge_rows[buf][t - 1][wu][1][0][lane], up_n = edge_rows[buf][t - 1][wu][1][1][lane];
-      const double dn_p = edge_rows[buf][t - 1][wd][0][0][lane], dn_n = edge_rows[buf][t - 1][wd][0][1][lane];
       double np[R], nn[R];
+      if (wanted) {
+        double bp[R], scp[SC ? R : 1], scn[SC ? R : 1];
+        // Two rows of both species at a time, stage by stage: four independent
+        // chains whose links stand far enough apart (an FP64 result is ready
+        // 8.5 cycles after its issue, which takes 4.5) for one wave to keep
+        // issuing while the other of its SIMD waits.  The strip's first row
+        // comes last: its upper neighbour comes from LDS.
 #pragma unroll
-      for (int r = 0; r < R; ++r) np[r] = nn[r] = 0.0;  // electrode planes and beyond hold zero
-      if (interior)  // block-uniform
+        for (int i0 = 0; i0 < R; i0 += 2) {
+          double xp[2], xn[2], yp[2], yn[2], ap[2], an[2];
+          constexpr int kPair = 2;
+          auto each = [&](auto f) {
 #pragma unroll
-      for (int i = 0; i < R; ++i) {
-        const int r = (i + 1) % R;  // the strip's first row last: its upper neighbour comes from LDS
-        const double pc = cpv[t - 1][r], nc = cnv[t - 1][r];
-        const double pxl = lane_from_left(pc), pxr = lane_from_right(pc);
-        const double nxl = lane_from_left(nc), nxr = lane_from_right(nc);
-        const double pyl = r > 0 ? cpv[t - 1][r - 1] : up_p, pyr = r < R - 1 ? cpv[t - 1][r + 1] : dn_p;
-        const double nyl = r > 0 ? cnv[t - 1][r - 1] : up_n, nyr = r < R - 1 ? cnv[t - 1][r + 1] : dn_n;
-        const double sink = beta * pc * nc;
-        const double net = pc - nc;
-        const double scp = SC ? gsp * pc * net : 0.0, scn = SC ? gsn * nc * net : 0.0;
-        double a = mp[t - 1][r] + cp.a0 * pc + cp.ax * (pxr + pxl) + cp.ay * (pyr + pyl) + cp.azp * vp[r] - sink;
-        double b = mn[t - 1][r] + cn.a0 * nc + cn.ax * (nxr + nxl) + cn.ay * (nyr + nyl) + cn.azp * vn[r] - sink;
-        if constexpr (SC) {  // (not "+ 0.0" without it: x + 0 is not folded away, as -0 + 0 = +0)
-          a += scp;
-          b += scn;
+            for (int u = 0; u < kPair; ++u)
+              if (i0 + u < R) f(u, (i0 + u + 1) % R);
+            __builtin_amdgcn_sched_barrier(0);
+          };
+          each([&](int u, int r) {
+            xp[u] = lane_from_left(cpv[t - 1][r]) + lane_from_right(cpv[t - 1][r]);
+            xn[u] = lane_from_left(cnv[t - 1][r]) + lane_from_right(cnv[t - 1][r]);
+          });
+          each([&](int u, int r) {
+            bp[r] = beta * cpv[t - 1][r];
+            ap[u] = mp[t - 1][r] + cp.a0 * cpv[t - 1][r];
+            an[u] = mn[t - 1][r] + cn.a0 * cnv[t - 1][r];
+          });
+          each([&](int u, int r) {
+            yp[u] = (r > 0 ? cpv[t - 1][r - 1] : up_t.x) + (r < R - 1 ? cpv[t - 1][r + 1] : dn_t.x);
+            yn[u] = (r > 0 ? cnv[t - 1][r - 1] : up_t.y) + (r < R - 1 ? cnv[t - 1][r + 1] : dn_t.y);
+          });
+          each([&](int u, int) {
+            ap[u] += cp.ax * xp[u];
+            an[u] += cn.ax * xn[u];
+          });
+          each([&](int u, int) {
+            ap[u] += cp.ay * yp[u];
+            an[u] += cn.ay * yn[u];
+          });
+          each([&](int u, int r) {
+            ap[u] += cp.azp * vp[r];
+            an[u] += cn.azp * vn[r];
+          });
+          each([&](int u, int r) {
+            ap[u] -= bp[r] * cnv[t - 1][r];
+            an[u] -= bp[r] * cnv[t - 1][r];
+            if constexpr (SC) {  // (not "+ 0.0" without it: x + 0 is not folded away, as -0 + 0 = +0)
+              const double net = cpv[t - 1][r] - cnv[t - 1][r];
+              scp[r] = gsp * cpv[t - 1][r] * net;
+              scn[r] = gsn * cnv[t - 1][r] * net;
+              ap[u] += scp[r];
+              an[u] += scn[r];
+            }
+            if (AB && !(in_x && in_y[r])) ap[u] = an[u] = 0.0;  // beyond an absorbing boundary
+            np[r] = ap[u];
+            nn[r] = an[u];
+          });
         }
-        if (AB && !(in_x && in_y[r])) a = b = 0.0;  // beyond an absorbing boundary
-        np[r] = a;
-        nn[r] = b;
-        if (counted && own_y[r]) {  // wave-uniform; the columns are masked at the end
-          acc[t - 1][0] += sink;
-          acc[t - 1][1] += a;
-          acc[t - 1][2] += b;
-          acc[t - 1][3] += fabs(a);
-          acc[t - 1][4] += fabs(b);
-          if constexpr (SC) {
-            acc[t - 1][5] += scp;
-            acc[t - 1][6] += scn;
-          }
-          if constexpr (AB) {
-            acc[t - 1][NE] += (cp.ax * miss_x + cp.ay * miss_y[r]) * pc;
-            acc[t - 1][NE + 1] += (cn.ax * miss_x + cn.ay * miss_y[r]) * nc;
+        if (counted) {  // the columns are masked at the end
+          auto tally = [&](int r) {
+            acc[t - 1][0] += bp[r] * cnv[t - 1][r];
+            acc[t - 1][1] += np[r];
+            acc[t - 1][2] += nn[r];
+            acc[t - 1][3] += fabs(np[r]);
+            acc[t - 1][4] += fabs(nn[r]);
+            if constexpr (SC) {
+              acc[t - 1][5] += scp[r];
+              acc[t - 1][6] += scn[r];
+            }
+            if constexpr (AB) {
+              acc[t - 1][NE] += (cp.ax * miss_x + cp.ay * miss_y[r]) * cpv[t - 1][r];
+              acc[t - 1][NE + 1] += (cn.ax * miss_x + cn.ay * miss_y[r]) * cnv[t - 1][r];
+            }
+          };
+          if (all_own) {  // wave-uniform
+#pragma unroll
+            for (int r = 0; r < R; ++r) tally(r);
+          } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+              if (own_y[r]) tally(r);
           }
         }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) np[r] = nn[r] = 0.0;
       }
-      if (PU && t == add_j && interior) {  // block-uniform: the pulse due after this level's step
-        const gchar* pp = uniform_ptr(add_p + (size_t)q * plane);
-        const gchar* pn = uniform_ptr(add_n + (size_t)q * plane);
+      if (PU && t == add_j && wanted) {  // block-uniform: the pulse due after this level's step
+        const rsrc_t pp = plane_rsrc(add_p + (size_t)q * plane, plane_bytes);
+        const rsrc_t pn = plane_rsrc(add_n + (size_t)q * plane, plane_bytes);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if (AB && !(in_x && in_y[r])) continue;  // beyond an absorbing boundary: stays zero
-          np[r] += *(const gdouble*)(pp + off[r]);
-          nn[r] += *(const gdouble*)(pn + off[r]);
+          np[r] += load_b64(pp, off[r]);
+          nn[r] += load_b64(pn, off[r]);
           if (counted && own_y[r] && own_x) add_max = fmax(add_max, fmax(np[r], nn[r]));
         }
       }
@@ -293,26 +383,21 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
         vp[r] = np[r];
         vn[r] = nn[r];
       }
+      // its edge rows, for the next iteration
+      edge_rows[buf ^ 1][t - 1][w][0][lane] = double2_t{cpv[t - 1][0], cnv[t - 1][0]};
+      edge_rows[buf ^ 1][t - 1][w][1][lane] = double2_t{cpv[t - 1][R - 1], cnv[t - 1][R - 1]};
     }
     // level T on plane K - T: the pass's output
     const int q = K - T;
     if (q >= za && q < zb) {
-      gchar* op = uniform_ptr(p.pout + (size_t)q * plane);
-      gchar* on = uniform_ptr(p.nout + (size_t)q * plane);
+      const rsrc_t op = plane_rsrc(p.pout + (size_t)q * plane, plane_bytes);
+      const rsrc_t on = plane_rsrc(p.nout + (size_t)q * plane, plane_bytes);
 #pragma unroll
       for (int r = 0; r < R; ++r)
         if (own_y[r] && own_x) {
-          __builtin_nontemporal_store(vp[r], (gdouble*)(op + off[r]));
-          __builtin_nontemporal_store(vn[r], (gdouble*)(on + off[r]));
+          store_b64_nt(op, off[r], vp[r]);
+          store_b64_nt(on, off[r], vn[r]);
         }
-    }
-    // edge rows of every level's current plane, for the next iteration
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      edge_rows[buf ^ 1][t][w][0][0][lane] = cpv[t][0];
-      edge_rows[buf ^ 1][t][w][0][1][lane] = cnv[t][0];
-      edge_rows[buf ^ 1][t][w][1][0][lane] = cpv[t][R - 1];
-      edge_rows[buf ^ 1][t][w][1][1][lane] = cnv[t][R - 1];
     }
   };
 
@@ -361,7 +446,11 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
       a[t * kAcc + 12] = 0.0;
     }
   }
-  block_sum_store<kAcc * T, kBNT>(a, partial_out, lds);
+  constexpr uint64_t kZero1 = (SC ? 0u : 3u << 9) | (AB ? 0u : 3u << 11), kLane1 = 0x1eu;
+  uint64_t constexpr kLevels = T == 2 ? 1ull | 1ull << kAcc : T == 3 ? 1ull | 1ull << kAcc | 1ull << 2 * kAcc
+                                                             : 1ull | 1ull << kAcc | 1ull << 2 * kAcc | 1ull << 3 * kAcc;
+  static_assert(T >= 2 && T <= 4 && 4 * kAcc <= 64, "slot masks");
+  block_sum_store<kAcc * T, kBNT, kZero1 * kLevels, kLane1 * kLevels>(a, partial_out, lds);
   if (PU && add_j > 0) {  // block-uniform
     __shared__ double wave_maxima[kBW];
     const double m = wave_max(add_max);

@@ -232,8 +232,8 @@ __device__ inline void plain_tile_step(const StepParams& p, const TileCoord t, d
   }
   // slots 9-10 (space charge) and 11-12 (escaped) are zero in instances
   // without those terms
-  constexpr uint32_t kZero = (SC ? 0u : 3u << 9) | (AB ? 0u : 3u << 11);
-  block_sum_store<kAcc, kSNT, kZero>(acc, partial_out, lds);
+  constexpr uint64_t kZero = (SC ? 0u : 3u << 9) | (AB ? 0u : 3u << 11);
+  block_sum_store<kAcc, kSNT, kZero, 0x1eu>(acc, partial_out, lds);
   if (add) {  // block-uniform
     __shared__ double wave_maxima[SY];
     const double m = wave_max(add_max);
@@ -450,8 +450,8 @@ __device__ inline void pair_tile_step(const StepParams& p, const TileCoord t, do
     acc[3] = edge[ty][2];
     acc[4] = edge[ty][3];
   }
-  constexpr uint32_t kZero = (SC ? 0u : 3u << 9) | (AB ? 0u : 3u << 11);
-  block_sum_store<kAcc, kSNT, kZero>(acc, partial_out, lds);
+  constexpr uint64_t kZero = (SC ? 0u : 3u << 9) | (AB ? 0u : 3u << 11);
+  block_sum_store<kAcc, kSNT, kZero, 0x1eu>(acc, partial_out, lds);
 }
 
 }  // namespace it
