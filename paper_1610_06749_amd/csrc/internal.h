@@ -25,6 +25,8 @@ constexpr int kAcc = 13;
 constexpr double kElementaryCharge = 1.602176634e-19;
 constexpr double kEpsilon0 = 8.8541878128e-14;
 constexpr int kMaxT = 8;  // largest number of fused steps per pass
+constexpr int kSectionT = 3;             // steps per pass of the section kernel (narrow chambers of a batch)
+constexpr int kSectionMaxThreads = 512;  // and its largest block
 
 // Coefficients of the explicit update of one species at an interior node:
 //   n' = a0 n + ax (n_{i+1} + n_{i-1}) + ay (n_{j+1} + n_{j-1})
@@ -206,13 +208,16 @@ hipError_t launch_reduce_steps(const StepParams& p, int nblocks, int T, hipStrea
 // step per pass); record_prev: the launch also records the previous pass's
 // step of every instance (false only for the first pass)
 // T > 1: T steps per launch with the blocked tile pass, R rows per thread
-// (tile_y and tile_x are then unused)
+// (tile_y and tile_x are then unused); section_threads > 0: with the section
+// pass instead, in blocks of that many threads (a
+// multiple of 64); crowded: its form for many blocks per CU
 hipError_t launch_batch_pass(const void* table, int ninst, int total_tiles, int tile_y, int tile_x, bool sc,
-                             bool ab, bool pu, int parity, bool record_prev, int T, int R, hipStream_t s);
+                             bool ab, bool pu, int parity, bool record_prev, int T, int R, int section_threads,
+                             bool crowded, hipStream_t s);
 // The same pass (recording the previous one) as a kernel node of `graph`
 // that depends on `dep` (null: none).
 hipError_t add_batch_pass_node(hipGraph_t graph, hipGraphNode_t dep, hipGraphNode_t* node, const void* table,
                                int ninst, int total_tiles, int tile_y, int tile_x, bool sc, bool ab, bool pu,
-                               int parity, int T, int R);
+                               int parity, int T, int R, int section_threads, bool crowded);
 
 }  // namespace it

@@ -11,84 +11,14 @@
 // past the stop, which no result reads.  Kernel boundaries order the passes;
 // the host captures a chain of passes in a HIP graph and replays it until
 // every instance has stopped.
+#include "batch_record.h"
 #include "stencil_blocked.h"
 
 namespace it {
 
+const void* batch_section(int R, int threads, bool crowded, bool pu);  // kernels_section.hip
+
 namespace {
-
-__device__ inline int find_instance(const BatchInstance* inst, int ninst, int L) {
-  int lo = 0, hi = ninst - 1;
-  while (lo < hi) {  // last instance with tile_begin <= L
-    const int mid = (lo + hi + 1) >> 1;
-    if (inst[mid].tile_begin <= L) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-// Records the previous pass's T steps of instance q (its partials are in
-// the buffer of the other parity), up to the instance's step limit: a pass
-// may run past it, and those steps are not recorded.
-//
-// Pulse trains (a period of at least T steps, so at most one pulse in a
-// pass): a pass computes steps c0 .. c0 + T - 1, and the pass in which a
-// pulse falls due adds it to the outputs of the level that computes the
-// step before it (pulse_add = j for a pulse at step c0 + j, j = 1..T; one
-// at c0 + T is thus added by the pass before the one it precedes).  The
-// recording block of a pass, which records the previous pass's steps
-// r0 .. r0 + T - 1, books the release of a pulse deposited before one of
-// them with that step (the first pulse's release, from the deposit, is
-// kept when step 0 is recorded), then sets the flag of the next pass, which
-// computes steps r0 + 2T .. r0 + 3T - 1.  The flags alternate by pass
-// parity, so the tile blocks of a pass read a flag the previous pass wrote.
-template <int NT>
-__device__ void record_previous(const BatchInstance& bi, int parity, int T) {
-  const StepParams& p = bi.sp[parity ^ 1];
-  if (p.state->done) return;
-  // the previous pass's tile count, which its own recording block stored
-  // (the host may have re-tiled the running instances since)
-  __shared__ int nprev;
-  if (threadIdx.x == 0 && threadIdx.y == 0) nprev = p.state->rec_ntiles;
-  __syncthreads();
-  __shared__ double totals[kAcc * kMaxT];
-  reduce_partials<NT>(p.partials, nprev, kAcc * T, kAcc * T, totals);
-  if (threadIdx.x == 0 && threadIdx.y == 0) {
-    RunState* st = p.state;
-    const int64_t step = st->steps;
-    const int Te = (int)min((int64_t)T, bi.max_steps - step);
-    const bool train = bi.npulses >= 2;
-    int inject = -1;
-    if (train) {
-      if (step == 0) {
-        st->pulse_q[0] = st->released;
-        st->pulse_q[1] = st->released_neg;
-      }
-      const int k = st->pulses_counted;
-      const int64_t s_k = (int64_t)k * bi.period_steps;
-      if (k < bi.npulses && s_k >= step && s_k < step + Te) {
-        inject = (int)(s_k - step);
-        st->pulses_counted = k + 1;
-      }
-    }
-    finalize_steps(st, p.trace, totals, Te, step, p.cp, p.cn, p.dV, p.stop_tol, p.min_stop_step, inject,
-                   train ? st->pulse_q[0] : 0.0, train ? st->pulse_q[1] : 0.0);
-    if (!st->done && st->steps >= bi.max_steps) {
-      st->done = 1;
-      st->by_limit = 1;
-    }
-    st->rec_ntiles = bi.ntiles;  // this pass's tiles, for the next recording block
-    if (train) {
-      // the next pass computes steps c1 .. c1 + T - 1; a pulse at or past
-      // the run's last step is never deposited
-      const int64_t c1 = step + 2 * T;
-      const int kf = st->pulses_flagged;
-      const int64_t s_due = (int64_t)kf * bi.period_steps;
-      const bool due = kf < bi.npulses && s_due > c1 && s_due <= c1 + T && s_due < bi.max_steps;
-      st->pulse_add[parity ^ 1] = due ? (int)(s_due - c1) : 0;
-      if (due) st->pulses_flagged = kf + 1;
-    }
-  }
-}
 
 // PU: some instance of the batch has a pulse train (its tile blocks add
 // the pulse when their instance's flag for this pass is set).
@@ -98,7 +28,7 @@ void batch_step_kernel(const BatchInstance* __restrict__ inst, int ninst, int to
                        int parity) {
   const int b = blockIdx.x;
   if (b >= 8 * per_xcd) {  // the recording blocks, one per instance
-    record_previous<kTX * SY>(inst[b - 8 * per_xcd], parity, 1);
+    record_previous(inst[b - 8 * per_xcd], parity, 1);
     return;
   }
   const int L = (b & 7) * per_xcd + (b >> 3);  // XCD-aware order over the whole list
@@ -131,7 +61,7 @@ void batch_blocked_kernel(const BatchInstance* __restrict__ inst, int ninst, int
                           int parity) {
   const int b = blockIdx.x;
   if (b >= 8 * per_xcd) {
-    record_previous<kBNT>(inst[b - 8 * per_xcd], parity, T);
+    record_previous(inst[b - 8 * per_xcd], parity, T);
     return;
   }
   const int L = blocked_tile_index(b, per_xcd);  // XCD-aware order over the whole list
@@ -225,23 +155,36 @@ const void* batch_kernel(int tile_y, int tile_x, bool sc, bool ab, bool pu, int*
   return batch_kernel_terms<8, 64>(sc, ab, pu);
 }
 
+// The kernel of a pass and its block (null if there is none).
+const void* pass_kernel(int tile_y, int tile_x, bool sc, bool ab, bool pu, int T, int R, int section_threads,
+                        bool crowded, dim3* block) {
+  if (section_threads > 0) {
+    *block = dim3(section_threads);
+    return sc || ab || T != kSectionT || section_threads % kWave ? nullptr
+                                                                          : batch_section(R, section_threads, crowded, pu);
+  }
+  int sy = kBW;  // blocked passes: blocks of 8 waves
+  const void* fn = T > 1 ? batch_blocked(T, R, sc, pu, ab) : batch_kernel(tile_y, tile_x, sc, ab, pu, &sy);
+  *block = dim3(kTX, sy);
+  return fn;
+}
+
 }  // namespace
 
 hipError_t add_batch_pass_node(hipGraph_t graph, hipGraphNode_t dep, hipGraphNode_t* node, const void* table,
                                int ninst, int total_tiles, int tile_y, int tile_x, bool sc, bool ab, bool pu,
-                               int parity, int T, int R) {
+                               int parity, int T, int R, int section_threads, bool crowded) {
   const BatchInstance* inst = (const BatchInstance*)table;
   int per_xcd = (total_tiles + 7) / 8;
-  int sy = 8;
-  const void* fn = T > 1 ? batch_blocked(T, R, sc, pu, ab) : batch_kernel(tile_y, tile_x, sc, ab, pu, &sy);
+  dim3 block;
+  const void* fn = pass_kernel(tile_y, tile_x, sc, ab, pu, T, R, section_threads, crowded, &block);
   if (!fn) return hipErrorInvalidValue;
-  if (T > 1) sy = kBW;  // blocks of 8 waves
   // the node copies the argument values when it is added
   void* args[] = {(void*)&inst, (void*)&ninst, (void*)&total_tiles, (void*)&per_xcd, (void*)&parity};
   hipKernelNodeParams kp{};
   kp.func = const_cast<void*>(fn);
   kp.gridDim = dim3(8 * per_xcd + ninst);  // tile blocks, then one recording block per instance
-  kp.blockDim = dim3(kTX, sy);
+  kp.blockDim = block;
   kp.sharedMemBytes = 0;
   kp.kernelParams = args;
   kp.extra = nullptr;
@@ -249,16 +192,16 @@ hipError_t add_batch_pass_node(hipGraph_t graph, hipGraphNode_t dep, hipGraphNod
 }
 
 hipError_t launch_batch_pass(const void* table, int ninst, int total_tiles, int tile_y, int tile_x, bool sc,
-                             bool ab, bool pu, int parity, bool record_prev, int T, int R, hipStream_t s) {
+                             bool ab, bool pu, int parity, bool record_prev, int T, int R, int section_threads,
+                             bool crowded, hipStream_t s) {
   const BatchInstance* inst = (const BatchInstance*)table;
   int per_xcd = (total_tiles + 7) / 8;
   const int nr = record_prev ? ninst : 0;
-  int sy = 8;
-  const void* fn = T > 1 ? batch_blocked(T, R, sc, pu, ab) : batch_kernel(tile_y, tile_x, sc, ab, pu, &sy);
+  dim3 block;
+  const void* fn = pass_kernel(tile_y, tile_x, sc, ab, pu, T, R, section_threads, crowded, &block);
   if (!fn) return hipErrorInvalidValue;
-  if (T > 1) sy = kBW;
   void* args[] = {(void*)&inst, (void*)&ninst, (void*)&total_tiles, (void*)&per_xcd, (void*)&parity};
-  return hipLaunchKernel(fn, dim3(8 * per_xcd + nr), dim3(kTX, sy), args, 0, s);
+  return hipLaunchKernel(fn, dim3(8 * per_xcd + nr), block, args, 0, s);
 }
 
 }  // namespace it

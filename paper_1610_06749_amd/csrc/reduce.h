@@ -101,10 +101,11 @@ __device__ inline bool arrive_last(unsigned* counter) {
 // for q < n.  Component q is reduced by wave q % W; its lanes take the blocks
 // in a fixed stride (8 independent loads in flight each) and the wave sums
 // them by a fixed butterfly, so all components finish in a few round trips.
-template <int NT>
+// NT: threads of the block (0: as launched).
+template <int NT = 0>
 __device__ inline void reduce_partials(const double* partials, int nblocks, int stride, int n,
                                        double* totals) {
-  constexpr int W = NT / kWave;
+  const int W = (NT > 0 ? NT : (int)(blockDim.x * blockDim.y)) / kWave;
   constexpr int kBatch = 8;
   const int tid = threadIdx.x + threadIdx.y * blockDim.x;
   const int wave = tid / kWave, lane = tid % kWave;

@@ -876,6 +876,112 @@ int batch_blocked_retile_z(const it_chamber* ch, const int* set, int n, int T, i
   return best_z;
 }
 
+// Section passes (kernels_section.hip): kSectionT steps per launch, a block per
+// chunk of planes of a chamber's whole cross-section, R rows per thread.
+struct Section {
+  int R = 0;        // 0: not taken
+  int threads = 0;  // of a block
+  bool crowded = false;  // the form for many blocks per CU
+};
+
+// Shortest chunk of the section tiles.  Their records fit the partial slots laid
+// out for blocked tiles of as many steps in chunks of kBlockedT planes.
+constexpr int kSectionMinZ = 6, kSectionMinNz = 3;
+static_assert(kSectionT == kBlockedT && kSectionMinZ >= kBlockedT, "partial slots of the section tiles");
+// latency of an iteration, in issue times of one block's iteration
+constexpr double kSectionLatency = 0.8, kSectionLatencyCrowded = 1.0;
+
+// Blocks of w waves that share a CU with `slots` waves per SIMD (measured with
+// kernels of 160 registers: a block whose waves do not fill the SIMDs evenly
+// shares its CU with none, but for three waves, of which four blocks fit three
+// slots).
+int section_resident(int w, int slots) {
+  if (w <= 2) return 4 * slots / w;
+  if (w == 3) return slots >= 3 ? 4 : 2;
+  return std::max(1, w % 4 == 0 ? 4 * slots / w : 1);
+}
+
+// The library's choice for a batch without space charge and absorbing
+// boundaries whose chambers are all narrow enough for a block: the rows per
+// thread (two to four, dividing every ny) with the most nodes resident on a CU
+// times the share of lanes that hold a node.  Not where most lanes would idle
+// (a chamber among much narrower ones), and a period of a pulse train has to
+// be kSectionT steps or more: the blocked pass then.  On MI355X, 192 chambers
+// of 24 x 24 nodes and up to 300 planes take 37 us per step while all run
+// (blocked pass: 103).
+Section batch_section_shape(const it_chamber* ch, int ninst, const int64_t* period_steps) {
+  Section best;
+  double best_score = 0.0;
+  for (int R = 2; R <= 4; ++R) {
+    Section s;
+    s.R = R;
+    double nodes = 0.0, planes = 0.0;
+    bool ok = true;
+    for (int q = 0; q < ninst && ok; ++q) {
+      const it_chamber& c = ch[q];
+      const double n = (double)c.nx * c.ny;
+      ok = c.ny % R == 0 && n <= (double)kSectionMaxThreads * R && c.nz >= kSectionMinNz && !c.space_charge &&
+           !c.lateral_bc && (c.n_pulses < 2 || period_steps[q] >= kSectionT);
+      if (!ok) break;
+      s.threads = std::max(s.threads, (c.nx * (c.ny / R) + 63) / 64 * 64);
+      nodes += n * (c.nz - 1);
+      planes += c.nz - 1;
+    }
+    if (!ok) continue;
+    const double held = nodes / (planes * s.threads * R);  // share of lanes with a node
+    const double score = nodes / planes * section_resident(s.threads / 64, R <= 3 ? 3 : 2) * held;
+    if (held >= 0.4 && score > best_score) {
+      best = s;
+      best_score = score;
+    }
+  }
+  return best;
+}
+
+// Section tiles of one chamber in chunks of zc planes.
+Tiling section_tiling(const it_chamber& c, int zc) {
+  Tiling t;
+  const int nint = c.nz - 1;
+  t.tiles_x = t.tiles_y = 1;
+  t.zc = std::max(1, std::min(zc, nint));
+  t.zchunks = t.ntiles = (nint + t.zc - 1) / t.zc;
+  t.per_xcd = (t.ntiles + 7) / 8;
+  t.grid = 8 * t.per_xcd;
+  return t;
+}
+
+// Chunk length of the section tiles of the running instances, and the kernel's
+// form: the pair that minimises the time of a CU with the most blocks,
+// iterations of a chunk times the time of an iteration (a latency part for
+// each round of co-resident blocks, an issue part for each block).
+int section_retile_z(const it_chamber* ch, const int* set, int n, Section* s) {
+  constexpr long kCUs = 256;
+  const int waves = s->threads / 64;
+  int most = 1;
+  for (int i = 0; i < n; ++i) most = std::max(most, ch[set[i]].nz - 1);
+  int best_z = most;
+  double best = 1e300;
+  for (int z = most; z >= std::min(most, kSectionMinZ); --z) {
+    long blocks = 0;
+    for (int i = 0; i < n; ++i) {
+      const int planes = ch[set[i]].nz - 1;
+      blocks += (planes + z - 1) / z;
+    }
+    const long per_cu = (blocks + kCUs - 1) / kCUs;
+    for (int crowded = 0; crowded <= (s->R <= 3 ? 1 : 0); ++crowded) {
+      const long resident = section_resident(waves, crowded ? 3 : 2), rounds = (per_cu + resident - 1) / resident;
+      const double latency = crowded ? kSectionLatencyCrowded : kSectionLatency;
+      const double cost = (z + 2.0 * kSectionT) * (latency * rounds + per_cu);
+      if (cost < best - 1e-9) {
+        best = cost;
+        best_z = z;
+        s->crowded = crowded != 0;
+      }
+    }
+  }
+  return best_z;
+}
+
 BatchLayout make_batch_layout(const it_chamber* ch, const int64_t* toff, int ninst, int rows, const it_exec* exec,
                               int tile_x, int T, int R) {
   BatchLayout B;
@@ -1342,10 +1448,16 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     if (requested_steps(exec) > 0) return IT_ENOTSUP;
     T = 1;
   }
-  const int R = T > 1 ? blocked_rows(T, exec ? exec->tile_y : 0) : 0;
+  int R = T > 1 ? blocked_rows(T, exec ? exec->tile_y : 0) : 0;
   const int tile_x = exec_tile_x(exec, ch, ninst, false);
   const BatchLayout B = make_batch_layout(ch, track_offsets, ninst, rows, exec, tile_x, T, R);
   if (!d_workspace || ws_bytes < B.total) return IT_EWORKSPACE;
+  Section sec;  // section passes instead of blocked ones, in the same workspace
+  if (T == kBlockedT && requested_steps(exec) == 0) sec = batch_section_shape(ch, ninst, period_steps.data());
+  if (sec.R) {
+    T = kSectionT;
+    R = sec.R;
+  }
   hipStream_t stream = (hipStream_t)stream_;
   char* ws = (char*)d_workspace;
   RunState* states = (RunState*)(ws + B.off_states);
@@ -1357,7 +1469,11 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
   // batch fills the machine, shorter ones when it does not (re-chosen for
   // the running instances whenever the table is rebuilt)
   const int z0 = T > 1 ? batch_blocked_z_chunk(exec) : 0;
-  const int zc_run = T > 1 ? batch_blocked_retile_z(ch, active.data(), ninst, T, R, z0) : 0;
+  auto choose_z = [&]() {
+    if (sec.R) return section_retile_z(ch, active.data(), (int)active.size(), &sec);
+    return T > 1 ? batch_blocked_retile_z(ch, active.data(), (int)active.size(), T, R, z0) : 0;
+  };
+  const int zc_run = choose_z();
   int total_tiles = 0;
   int64_t max_steps_all = 0;
   for (int q = 0; q < ninst; ++q) {
@@ -1381,7 +1497,7 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
 
     const Coef cp = species_coef(c, dts[q], 0), cn = species_coef(c, dts[q], 1);
     const double dz = c->gap / c->nz, dV = c->dx * c->dy * dz;
-    const Tiling ts = batch_tiling(*c, T, R, rows, exec, tile_x, zc_run);
+    const Tiling ts = sec.R ? section_tiling(*c, zc_run) : batch_tiling(*c, T, R, rows, exec, tile_x, zc_run);
     const Tiling td = deposit_tiling(c->nx, c->ny, c->nz);
     BatchInstance& bi = table[q];
     for (int par = 0; par < 2; ++par) {
@@ -1486,9 +1602,9 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
   // state for the next).
   auto retile = [&]() {
     if (T == 1) return;
-    const int z = batch_blocked_retile_z(ch, active.data(), (int)active.size(), T, R, z0);
+    const int z = choose_z();
     for (int q : active) {
-      const Tiling ts = batch_blocked_tiling(ch[q], T, R, z);
+      const Tiling ts = sec.R ? section_tiling(ch[q], z) : batch_blocked_tiling(ch[q], T, R, z);
       for (int par = 0; par < 2; ++par) {
         StepParams& sp = table[q].sp[par];
         sp.tiles_x = ts.tiles_x;
@@ -1523,7 +1639,7 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     for (int k = 0; k < passes_per_graph; ++k) {
       hipGraphNode_t node = nullptr;
       if (add_batch_pass_node(graph, prev, &node, ws + B.off_table, (int)t.size(), tiles, rows, tile_x, any_sc,
-                              any_ab, any_pu, (parity0 + k) & 1, T, R) != hipSuccess)
+                              any_ab, any_pu, (parity0 + k) & 1, T, R, sec.threads, sec.crowded) != hipSuccess)
         return IT_EHIP;
       prev = node;
     }
@@ -1543,7 +1659,7 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     int tiles = 0;
     for (int q = 0; q < ninst; ++q) tiles += table[q].ntiles;
     if (launch_batch_pass(ws + B.off_table, ninst, tiles, rows, tile_x, any_sc, any_ab, any_pu, 0, false, T, R,
-                          stream) !=
+                          sec.threads, sec.crowded, stream) !=
         hipSuccess) {
       release_graph();
       return IT_EHIP;

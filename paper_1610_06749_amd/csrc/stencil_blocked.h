@@ -64,6 +64,8 @@ __device__ inline double load_b64(rsrc_t r, unsigned off) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
 }
 
+constexpr unsigned kOutside = 0xfffffff0u;  // an offset beyond every plane
+
 __device__ inline void store_b64(rsrc_t r, unsigned off, double v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2_t, v), r, off, 0, 0);
 }
@@ -389,15 +391,18 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
     }
     // level T on plane K - T: the pass's output
     const int q = K - T;
-    if (q >= za && q < zb) {
-      const rsrc_t op = plane_rsrc(p.pout + (size_t)q * plane, plane_bytes);
-      const rsrc_t on = plane_rsrc(p.nout + (size_t)q * plane, plane_bytes);
+    // The stores are not branched around (what is not owned, or not the
+    // chunk's, goes to an offset outside the plane), so that the number of
+    // accesses in flight is known and the wait for a plane of level 0 is not
+    // one for the stores after it too.
+    const bool out = q >= za && q < zb;
+    const size_t o = (size_t)max(q, 0) * plane;
+    const rsrc_t op = plane_rsrc(p.pout + o, plane_bytes), on = plane_rsrc(p.nout + o, plane_bytes);
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (own_y[r] && own_x) {
-          store_b64_nt(op, off[r], vp[r]);
-          store_b64_nt(on, off[r], vn[r]);
-        }
+    for (int r = 0; r < R; ++r) {
+      const unsigned at = own_x && own_y[r] && out ? off[r] : kOutside;
+      store_b64_nt(op, at, vp[r]);
+      store_b64_nt(on, at, vn[r]);
     }
   };
 
