@@ -56,7 +56,7 @@ struct RunState {
   double e_left;            // electrons in flight after the last electron step
   int64_t e_steps;          // electron-phase steps recorded
   int32_t e_done;           // 1 once the electrons are collected
-  int32_t e_pad;
+  uint32_t dep_arrived;     // deposit tiles done (0 between deposits)
   int64_t steps;            // steps recorded so far
   int32_t done;             // 1 once the stop criterion (or a non-finite tally) is met
   int32_t flags;            // IT_FLAG_NONFINITE
@@ -118,7 +118,6 @@ struct StepParams {
   int64_t step0;            // index of the step this launch computes
   int64_t min_stop_step;    // the stop criterion is tested only from this step on
   double* partials;         // [gridDim][kAcc * T]
-  unsigned* counter;
   RunState* state;
   double* trace;            // [max_steps][IT_TRACE_COLS]
   // when set, one extra block of the launch reduces the partials of the
@@ -133,8 +132,12 @@ struct StepParams {
 struct DepositParams {
   double* pos;
   double* neg;
+  int fresh;                // 1: the fields hold nothing yet (written without being read); 0: added to
+  double *pos2, *neg2;      // fresh: the other field pair (its electrode planes are cleared)
+  double *pulse_pos, *pulse_neg;  // when set, the densities go here too (a batch's pulse train)
   int nx, ny, nz;
-  int tiles_x, tiles_y, zchunks, zc, ntiles, per_xcd;
+  int tiles, zc, ntiles;    // tiles of 256 nodes per plane, planes per chunk, tiles in all
+  int tile_begin;           // batches: first tile of this chamber in the launch
   double dx, dy, dz, half_gap, Lx, Ly;
   int absorbing;            // 1: transverse offsets as they are; 0: nearest periodic image
   double uniform;           // uniform density added at this deposit (0 if none)
@@ -145,12 +148,11 @@ struct DepositParams {
   double dV, beta;
   int same_radii;           // 1: every track gives both species the same radius
   // free electrons: the negative charge splits into negative ions
-  // (1 - e^{-a z}) and electrons (fraction pfree) written to `ele`
+  // (1 - e^{-a z}) and electrons (fraction pfree) written to `ele` (fresh only)
   int free_e;
   double attach, pfree;
-  double* ele;
-  double* partials;         // [gridDim][5]
-  unsigned* counter;
+  double *ele, *ele2;
+  double* partials;         // [ntiles][5]
   RunState* state;
 };
 
@@ -202,6 +204,8 @@ int plain_tile_rows(int tile_y, int tile_x);
 hipError_t launch_step_plain(const StepParams& p, int tile_y, int tile_x, hipStream_t s,
                              hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr, bool fused = false);
 hipError_t launch_deposit(const DepositParams& p, hipStream_t s);
+// The first deposits of n chambers (device table), `tiles` tiles in all.
+hipError_t launch_deposit_batch(const DepositParams* table, int n, int tiles, hipStream_t s);
 hipError_t launch_reduce_steps(const StepParams& p, int nblocks, int T, hipStream_t s);
 // sc: some instance has the space-charge term on; ab: some instance has
 // absorbing lateral boundaries; pu: some instance has a pulse train (one

@@ -1,4 +1,4 @@
-// Plain one-step stencil kernel and the track deposition kernel (gfx950).
+// Plain one-step stencil kernel (gfx950).
 //
 // Step kernel: one explicit time step of both ion species (eq. theEquation
 // with the Appendix's difference scheme, written as per-node coefficients),
@@ -18,8 +18,6 @@
 #include "stencil_plain.h"
 
 namespace it {
-
-constexpr int kTY = 4, kNT = kTX * kTY;  // deposition tile
 
 // With p.prev_partials set, the launch has one block more than tiles: that
 // block sums the previous step's partials in a fixed order and records the
@@ -112,153 +110,6 @@ hipError_t launch_step_plain(const StepParams& p, int tile_y, int tile_x, hipStr
   if (ev_end && hipEventRecord(ev_end, s) != hipSuccess) return hipErrorInvalidValue;
   if (fused) return hipSuccess;  // the next launch (or a closing reduction) records this step
   return launch_reduce_steps(p, grid, 1, s);
-}
-
-// ---------------------------------------------------------------------------
-// Deposition (eq. Gaussian around each track axis, eq. linear_density for N0).
-// Each thread owns one transverse column of a tile and a chunk of planes.
-// Tracks parallel to the field give the same density on every plane, so
-// their sum is formed once per column; tilted tracks are evaluated per node.
-// The perpendicular distance is |w x u| with w the node's offset from the
-// axis point (x0, y0, d/2), its transverse part wrapped to the nearest
-// periodic image (taken as it is with absorbing lateral boundaries); the
-// profile is cut at r^2 > (8 b)^2.
-// ---------------------------------------------------------------------------
-
-__device__ inline double wrap_near(double d, double L) { return d - L * floor(d / L + 0.5); }
-
-__device__ inline double lateral_offset(const DepositParams& p, double d, double L) {
-  return p.absorbing ? d : wrap_near(d, L);
-}
-
-__device__ inline double axis_r2(const DepTrack& tr, double wx, double wy, double wz) {
-  const double cx = wy * tr.uz - wz * tr.uy;
-  const double cy = wz * tr.ux - wx * tr.uz;
-  const double cz = wx * tr.uy - wy * tr.ux;
-  return cx * cx + cy * cy + cz * cz;
-}
-
-// Densities of the positive and (with its own radius) negative ions.
-__device__ inline void track_values(const DepTrack& tr, double wx, double wy, double wz, bool same,
-                                    double& dp, double& dn) {
-  const double r2 = axis_r2(tr, wx, wy, wz);
-  dp = r2 > tr.cut2 ? 0.0 : tr.peak * exp(-r2 * tr.inv_b2);
-  dn = same ? dp : (r2 > tr.cut2_n ? 0.0 : tr.peak_n * exp(-r2 * tr.inv_b2_n));
-}
-
-__global__ __launch_bounds__(kNT) void deposit_kernel(DepositParams p) {
-  constexpr int NP = 5;  // partials: released n+, n- ions, electrons, negative charge; max density
-  __shared__ double lds[(kNT / kWave) * NP];
-  double acc[NP] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  const bool same = p.same_radii != 0;
-  const TileCoord t = decode_tile(p.tiles_x, p.tiles_y, p.ntiles, p.per_xcd);
-  const int i = t.tx * kTX + threadIdx.x;
-  const int j = t.ty * kTY + threadIdx.y;
-  if (t.valid && i < p.nx && j < p.ny) {
-    const int k0 = 1 + t.zc * p.zc;
-    const int k1 = min(k0 + p.zc, p.nz);
-    const double x = i * p.dx, y = j * p.dy;
-    double g0p = p.uniform, g0n = p.uniform;
-    for (int q = 0; q < p.npar; ++q) {
-      const DepTrack tr = p.par[q];
-      double dp, dn;
-      track_values(tr, lateral_offset(p, x - tr.x0, p.Lx), lateral_offset(p, y - tr.y0, p.Ly), 0.0, same, dp,
-                   dn);
-      g0p += dp;
-      g0n += dn;
-    }
-    const size_t plane = (size_t)p.nx * p.ny;
-    size_t c = (size_t)k0 * plane + (size_t)j * p.nx + i;
-    for (int k = k0; k < k1; ++k, c += plane) {
-      double d_p = g0p, d_n = g0n;
-      if (p.ntilt) {
-        const double wz = k * p.dz - p.half_gap;
-        for (int q = 0; q < p.ntilt; ++q) {
-          const DepTrack tr = p.tilt[q];
-          double dp, dn;
-          track_values(tr, lateral_offset(p, x - tr.x0, p.Lx), lateral_offset(p, y - tr.y0, p.Ly), wz, same,
-                       dp, dn);
-          d_p += dp;
-          d_n += dn;
-        }
-      }
-      const double a = p.pos[c] + d_p;
-      p.pos[c] = a;
-      acc[0] += d_p;
-      acc[3] += d_n;
-      if (p.free_e) {  // eq. ion_elec_distribution: ions (1 - e^{-a z}), electrons p
-        const double di = d_n * -expm1(-p.attach * (k * p.dz)), de = d_n * p.pfree;
-        const double b = p.neg[c] + di, e = p.ele[c] + de;
-        p.neg[c] = b;
-        p.ele[c] = e;
-        acc[1] += di;
-        acc[2] += de;
-        acc[4] = fmax(acc[4], fmax(a, b + e));
-      } else {
-        const double b = p.neg[c] + d_n;
-        p.neg[c] = b;
-        acc[1] += d_n;
-        acc[4] = fmax(acc[4], fmax(a, b));
-      }
-    }
-  }
-  const int tid = threadIdx.x + threadIdx.y * blockDim.x;
-  {
-    double v[NP];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = wave_sum(acc[q]);
-    v[4] = wave_max(acc[4]);
-    if (tid % kWave == 0)
-      for (int q = 0; q < NP; ++q) lds[(tid / kWave) * NP + q] = v[q];
-    __syncthreads();
-    if (tid == 0) {
-      double r[NP];
-      for (int q = 0; q < NP; ++q) r[q] = lds[q];
-      for (int w = 1; w < kNT / kWave; ++w) {
-        for (int q = 0; q < 4; ++q) r[q] += lds[w * NP + q];
-        r[4] = fmax(r[4], lds[w * NP + 4]);
-      }
-      for (int q = 0; q < NP; ++q) p.partials[(size_t)blockIdx.x * NP + q] = r[q];
-    }
-  }
-  if (!arrive_last<kNT>(p.counter)) return;
-  {
-    double v[NP] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int b = tid; b < (int)gridDim.x; b += kNT) {
-      for (int q = 0; q < 4; ++q) v[q] += p.partials[(size_t)b * NP + q];
-      v[4] = fmax(v[4], p.partials[(size_t)b * NP + 4]);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = wave_sum(v[q]);
-    v[4] = wave_max(v[4]);
-    __syncthreads();
-    if (tid % kWave == 0)
-      for (int q = 0; q < NP; ++q) lds[(tid / kWave) * NP + q] = v[q];
-    __syncthreads();
-    if (tid == 0) {
-      double r[NP];
-      for (int q = 0; q < NP; ++q) r[q] = lds[q];
-      for (int w = 1; w < kNT / kWave; ++w) {
-        for (int q = 0; q < 4; ++q) r[q] += lds[w * NP + q];
-        r[4] = fmax(r[4], lds[w * NP + 4]);
-      }
-      RunState* st = p.state;
-      st->released += r[0] * p.dV;
-      st->released_pending += r[0] * p.dV;
-      st->released_neg += r[1] * p.dV;
-      st->released_pending_neg += r[1] * p.dV;
-      st->released_e += r[2] * p.dV;
-      st->released_q += r[3] * p.dV;
-      st->max_beta_n = fmax(st->max_beta_n, p.beta * r[4]);
-      *p.counter = 0u;
-    }
-  }
-}
-
-hipError_t launch_deposit(const DepositParams& p, hipStream_t s) {
-  const int grid = 8 * p.per_xcd;
-  hipLaunchKernelGGL(deposit_kernel, dim3(grid), dim3(kTX, kTY), 0, s, p);
-  return hipGetLastError();
 }
 
 }  // namespace it

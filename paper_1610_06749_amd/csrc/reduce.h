@@ -82,15 +82,16 @@ __device__ inline void block_sum_store(double (&acc)[N], double* out, double* ld
 // the device-scope fence of every block costs an L2 write-back, so the
 // stepping kernels leave their partials to the next launch, whose kernel
 // boundary makes them visible.)
+// nblocks: blocks that take part.
 template <int NT>
-__device__ inline bool arrive_last(unsigned* counter) {
+__device__ inline bool arrive_last(unsigned* counter, unsigned nblocks) {
   __shared__ int last;
   __syncthreads();
   const int tid = threadIdx.x + threadIdx.y * blockDim.x;
   if (tid == 0) {
     __threadfence();
     const unsigned ticket = atomicAdd(counter, 1u);
-    last = ticket == gridDim.x * gridDim.y * gridDim.z - 1;
+    last = ticket == nblocks - 1;
   }
   __syncthreads();
   if (last) __threadfence();

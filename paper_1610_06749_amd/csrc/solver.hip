@@ -352,14 +352,23 @@ int check_exec_ws(const it_chamber* ch, const it_exec* ex, int T, const void* ws
   return IT_OK;
 }
 
-Tiling deposit_tiling(int nx, int ny, int nz) {
-  const long cols = (long)((nx + 63) / 64) * ((ny + 3) / 4);
+// Tiles of the deposit kernel: 256 nodes of a plane by a chunk of planes (a
+// multiple of four), about `target` of them: 2048 for a single chamber, in a
+// batch 8192 among all chambers (each tile ends with a device-wide fence).
+struct DepositTiling {
+  int tiles, zc, ntiles;
+};
+
+DepositTiling deposit_tiling(int nx, int ny, int nz, int ninst) {
+  const long target = ninst > 1 ? std::max(32, 8192 / ninst) : 2048;
+  DepositTiling t;
+  t.tiles = (int)(((long)nx * ny + 255) / 256);
   const int nint = nz - 1;
-  long want = std::max<long>(1, (2048 + cols - 1) / cols);
+  long want = std::max<long>(1, (target + t.tiles - 1) / t.tiles);
   want = std::min<long>(want, nint);
-  int zc = (int)((nint + want - 1) / want);
-  zc = std::max(zc, std::min(4, nint));
-  return make_tiling(nx, ny, nz, 4, zc);
+  t.zc = ((int)((nint + want - 1) / want) + 3) / 4 * 4;
+  t.ntiles = t.tiles * ((nint + t.zc - 1) / t.zc);
+  return t;
 }
 
 struct Layout {
@@ -367,7 +376,6 @@ struct Layout {
   size_t off_field[4];
   size_t off_ele[2];        // electron densities (free-electron runs only)
   size_t off_partials, partial_doubles;
-  size_t off_counter;
   size_t off_state;
   size_t off_tracks;
   size_t off_trace;
@@ -377,7 +385,7 @@ struct Layout {
 size_t max_grid(const it_chamber* ch) {
   // the smallest z chunk gives the most stepping blocks of any launch shape
   size_t g = std::max((size_t)step_tiling(ch->nx, ch->ny, ch->nz, 8, kMinZChunk).grid,
-                      (size_t)deposit_tiling(ch->nx, ch->ny, ch->nz).grid);
+                      (size_t)deposit_tiling(ch->nx, ch->ny, ch->nz, 1).ntiles);
   g = std::max(g, (size_t)step_tiling(ch->nx, ch->ny, ch->nz, 16, kMinZChunk, 32).grid);
   for (int T = 2; T <= kMaxT; ++T)
     for (int R = 1; R <= 8; ++R) {  // every rows-per-thread choice the caller can make
@@ -408,8 +416,6 @@ Layout make_layout(const it_chamber* ch, int64_t ntracks) {
   L.partial_doubles = 2 * max_grid(ch) * (size_t)std::max(kAcc, kAcc3);
   L.off_partials = off;
   off = align_up(off + L.partial_doubles * sizeof(double));
-  L.off_counter = off;
-  off = align_up(off + 64 * sizeof(unsigned));
   L.off_state = off;
   off = align_up(off + sizeof(RunState));
   L.off_tracks = off;
@@ -503,19 +509,17 @@ DepTrack prepare_track(const it_chamber* ch, const it_track& t) {
 
 // Deposit parameters common to every deposit of a chamber (fields, tracks,
 // partials and state pointers are filled in by the caller).
-DepositParams base_deposit(const it_chamber* ch, double dt, const Tiling& td) {
+DepositParams base_deposit(const it_chamber* ch, double dt, int ninst) {
   DepositParams dp;
   std::memset(&dp, 0, sizeof(dp));
   const double dz = ch->gap / ch->nz;
   dp.nx = ch->nx;
   dp.ny = ch->ny;
   dp.nz = ch->nz;
-  dp.tiles_x = td.tiles_x;
-  dp.tiles_y = td.tiles_y;
-  dp.zchunks = td.zchunks;
+  const DepositTiling td = deposit_tiling(ch->nx, ch->ny, ch->nz, ninst);
+  dp.tiles = td.tiles;
   dp.zc = td.zc;
   dp.ntiles = td.ntiles;
-  dp.per_xcd = td.per_xcd;
   dp.dx = ch->dx;
   dp.dy = ch->dy;
   dp.dz = dz;
@@ -538,8 +542,9 @@ struct Event {
 // up to T steps, cut at deposit steps, and reads the run state back every
 // `check_every` steps (two checks in flight) to stop once the device has
 // flagged completion.
-int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const Layout& L,
-             const std::vector<Event>& events, const std::vector<DepTrack>& dev_tracks, int same_r,
+// pos0, neg0: the first field pair (the workspace's, or a caller's own).
+int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const Layout& L, double* pos0,
+             double* neg0, const std::vector<Event>& events, int same_r,
              int64_t nsteps, int64_t min_stop_step, double stop_tol, int T, hipStream_t stream, HostSlots& hs,
              RunState* final_state, int* passes_issued) {
   const int exec_rc = check_exec(ch, ex, T);
@@ -549,14 +554,11 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
   const bool span = ex && ex->timing_events && ex->timing_span && ex->n_timing_events >= 2;
   const int n_timing = ex && ex->timing_events && !span ? std::max(ex->n_timing_events, 0) / 2 : 0;
 
-  double* field[4];
-  for (int f = 0; f < 4; ++f) field[f] = (double*)(ws + L.off_field[f]);
+  double* field[4] = {pos0, neg0, (double*)(ws + L.off_field[2]), (double*)(ws + L.off_field[3])};
   double* partials = (double*)(ws + L.off_partials);
-  unsigned* counter = (unsigned*)(ws + L.off_counter);
   RunState* state = (RunState*)(ws + L.off_state);
   DepTrack* tracks = (DepTrack*)(ws + L.off_tracks);
   double* trace = (double*)(ws + L.off_trace);
-  (void)dev_tracks;
 
   const Coef cp = species_coef(ch, dt, 0), cn = species_coef(ch, dt, 1);
   const double dz = ch->gap / ch->nz;
@@ -568,7 +570,6 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
   }
   const int rows = tx == 32 ? 16 : resolve_rows(tile_y, ch->ny);
   const Tiling tp = step_tiling(ch->nx, ch->ny, ch->nz, rows, exec_z_chunk(ex), tx);
-  const Tiling td = deposit_tiling(ch->nx, ch->ny, ch->nz);
 
   RunState* slots = hs.p;
   // read-backs in flight: two with the caller's page-locked buffer, else one
@@ -589,7 +590,6 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
   sp.stop_tol = stop_tol;
   sp.min_stop_step = min_stop_step;
   sp.partials = partials;
-  sp.counter = counter;
   sp.state = state;
   sp.trace = trace;
   sp.prev_partials = nullptr;
@@ -597,10 +597,9 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
   sp.prev_T = 1;
   sp.prev_step = 0;
 
-  DepositParams dp = base_deposit(ch, dt, td);
+  DepositParams dp = base_deposit(ch, dt, 1);
   dp.same_radii = same_r;
   dp.partials = partials;
-  dp.counter = counter;
   dp.state = state;
 
   int cur = 0;  // field pair index: 0 -> (field0, field1), 1 -> (field2, field3)
@@ -750,15 +749,16 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
 
 struct InstLayout {
   size_t off_field[4], field_elems;
-  size_t off_partials, off_counter, off_tracks;
+  size_t off_partials;
   size_t off_pulse[2];  // the first pulse's densities (pulse trains only)
   int slots;        // partial slots per pass: the most stepping tiles the run can use
 };
 
 struct BatchLayout {
   std::vector<InstLayout> inst;
+  size_t off_tracks;  // DepTrack of all chambers
   size_t off_states;  // RunState[ninst], contiguous for one read-back
-  size_t off_table;   // BatchInstance[ninst]
+  size_t off_table;   // BatchInstance[ninst] (before the first pass: DepositParams[ninst])
   size_t total;
 };
 
@@ -999,14 +999,10 @@ BatchLayout make_batch_layout(const it_chamber* ch, const int64_t* toff, int nin
     // (blocked tiles are re-chunked as instances stop)
     const int zmin = T > 1 ? batch_blocked_min_z(batch_blocked_z_chunk(exec), T) : 0;
     const Tiling ts = batch_tiling(c, T, R, rows, exec, tile_x, zmin);
-    const Tiling td = deposit_tiling(c.nx, c.ny, c.nz);
+    const DepositTiling td = deposit_tiling(c.nx, c.ny, c.nz, ninst);
     L.slots = ts.ntiles;
     L.off_partials = off;  // two halves of step partials (alternate passes); the deposit uses the start
-    off = align_up(off + std::max((size_t)2 * ts.ntiles * kAcc * T, (size_t)td.grid * 5) * sizeof(double));
-    L.off_counter = off;
-    off = align_up(off + 64 * sizeof(unsigned));
-    L.off_tracks = off;
-    off = align_up(off + (size_t)std::max<int64_t>(toff[q + 1] - toff[q], 1) * sizeof(DepTrack));
+    off = align_up(off + std::max((size_t)2 * ts.ntiles * kAcc * T, (size_t)td.ntiles * 5) * sizeof(double));
     L.off_pulse[0] = L.off_pulse[1] = 0;
     if (c.n_pulses >= 2)
       for (int f = 0; f < 2; ++f) {
@@ -1014,6 +1010,8 @@ BatchLayout make_batch_layout(const it_chamber* ch, const int64_t* toff, int nin
         off = align_up(off + L.field_elems * sizeof(double));
       }
   }
+  B.off_tracks = off;
+  off = align_up(off + (size_t)std::max<int64_t>(toff[ninst], 1) * sizeof(DepTrack));
   B.off_states = off;
   off = align_up(off + (size_t)ninst * sizeof(RunState));
   B.off_table = off;
@@ -1301,9 +1299,6 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
     }
   }
 
-  for (int f = 0; f < 4; ++f)
-    HIP_TRY(hipMemsetAsync(ws + L.off_field[f], 0, L.field_elems * sizeof(double), stream));
-  HIP_TRY(hipMemsetAsync(ws + L.off_counter, 0, 64 * sizeof(unsigned), stream));
   RunState init = initial_run_state();
   if (train) init.period_step = (ch->n_pulses - 1) * period_steps;
   HIP_TRY(hipMemcpyAsync(ws + L.off_state, &init, sizeof(init), hipMemcpyHostToDevice, stream));
@@ -1311,35 +1306,38 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
     HIP_TRY(hipMemcpyAsync(ws + L.off_tracks, dev.data(), dev.size() * sizeof(DepTrack),
                            hipMemcpyHostToDevice, stream));
 
-  int64_t e_steps = 0;
-  if (fe) {
-    // the pulse, split into ions and electrons, then the electron phase;
-    // the ion phase below starts from its end with no further deposits
-    for (int f = 0; f < 2; ++f)
-      HIP_TRY(hipMemsetAsync(ws + L.off_ele[f], 0, L.field_elems * sizeof(double), stream));
-    DepositParams dp = base_deposit(ch, dt, deposit_tiling(ch->nx, ch->ny, ch->nz));
-    dp.pos = (double*)(ws + L.off_field[0]);
-    dp.neg = (double*)(ws + L.off_field[1]);
+  // the deposit of step 0 (of nothing, if none is due then) writes the fields
+  DepositParams dp = base_deposit(ch, dt, 1);
+  dp.fresh = 1;
+  dp.pos = (double*)(ws + L.off_field[0]);
+  dp.neg = (double*)(ws + L.off_field[1]);
+  dp.pos2 = (double*)(ws + L.off_field[2]);
+  dp.neg2 = (double*)(ws + L.off_field[3]);
+  if (!events.empty() && events[0].step == 0) {
+    const Event& e = events[0];
+    const DepTrack* tr_dev = (const DepTrack*)(ws + L.off_tracks);
+    dp.uniform = e.uniform ? ch->uniform_n0 : 0.0;
+    dp.par = tr_dev + e.par_begin;
+    dp.npar = (int)e.par_count;
+    dp.tilt = tr_dev + e.tilt_begin;
+    dp.ntilt = (int)e.tilt_count;
+    events.erase(events.begin());
+  }
+  dp.same_radii = same_radii(tracks, ntracks);
+  dp.partials = (double*)(ws + L.off_partials);
+  dp.state = (RunState*)(ws + L.off_state);
+  if (fe) {  // the pulse, split into ions and electrons
     dp.ele = (double*)(ws + L.off_ele[0]);
+    dp.ele2 = (double*)(ws + L.off_ele[1]);
     dp.free_e = 1;
     dp.attach = ch->attach_coeff;
     dp.pfree = free_fraction(ch->attach_coeff, ch->gap);
-    dp.uniform = ch->uniform_n0;
-    const DepTrack* tr_dev = (const DepTrack*)(ws + L.off_tracks);
-    if (!events.empty()) {
-      dp.par = tr_dev + events[0].par_begin;
-      dp.npar = (int)events[0].par_count;
-      dp.tilt = tr_dev + events[0].tilt_begin;
-      dp.ntilt = (int)events[0].tilt_count;
-    }
-    dp.same_radii = same_radii(tracks, ntracks);
-    dp.partials = (double*)(ws + L.off_partials);
-    dp.counter = (unsigned*)(ws + L.off_counter);
-    dp.state = (RunState*)(ws + L.off_state);
-    if (!events.empty()) HIP_TRY(launch_deposit(dp, stream));
+  }
+  HIP_TRY(launch_deposit(dp, stream));
+  int64_t e_steps = 0;
+  if (fe) {  // the electron phase; the ion phase below starts from its end
     rc = electron_phase(ch, dt, ws, L, stream, hs.p, &e_steps);
     if (rc) return rc;
-    events.clear();
     last_dep = 0;
   }
 
@@ -1350,8 +1348,8 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
   const int64_t ion_steps = train ? std::min<int64_t>(ch->n_pulses * period_steps, limit) : limit;
   const int64_t min_stop = train ? INT64_MAX : std::max<int64_t>(last_dep, 0);
   if (ion_steps > 0) {
-    rc = run_loop(ch, dt, exec, ws, L, events, dev, same_radii(tracks, ntracks), ion_steps, min_stop,
-                  ch->stop_tol, T, stream, hs, &fin, &issued);
+    rc = run_loop(ch, dt, exec, ws, L, (double*)(ws + L.off_field[0]), (double*)(ws + L.off_field[1]), events,
+                  same_radii(tracks, ntracks), ion_steps, min_stop, ch->stop_tol, T, stream, hs, &fin, &issued);
     if (rc) return rc;
   } else {
     HIP_TRY(hipMemcpyAsync(hs.p, ws + L.off_state, sizeof(fin), hipMemcpyDeviceToHost, stream));
@@ -1474,8 +1472,12 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     return T > 1 ? batch_blocked_retile_z(ch, active.data(), (int)active.size(), T, R, z0) : 0;
   };
   const int zc_run = choose_z();
-  int total_tiles = 0;
+  int total_tiles = 0, deposit_tiles = 0;
   int64_t max_steps_all = 0;
+  // every chamber's tracks, run state and first deposit go over in one copy each
+  std::vector<DepTrack> all_tracks(track_offsets[ninst]);
+  std::vector<RunState> init_states(ninst);
+  std::vector<DepositParams> deposits(ninst);
   for (int q = 0; q < ninst; ++q) {
     const it_chamber* c = &ch[q];
     const int64_t n = track_offsets[q + 1] - track_offsets[q];
@@ -1483,22 +1485,15 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     const bool train = c->n_pulses >= 2;
     const int64_t m = period_steps[q];
     const InstLayout& L = B.inst[q];
-    for (int f = 0; f < 4; ++f)
-      HIP_TRY(hipMemsetAsync(ws + L.off_field[f], 0, L.field_elems * sizeof(double), stream));
-    HIP_TRY(hipMemsetAsync(ws + L.off_counter, 0, 64 * sizeof(unsigned), stream));
-    std::vector<DepTrack> dev(n);
-    for (int64_t k = 0; k < n; ++k) {  // parallel tracks first, as the kernel expects
-      dev[k] = prepare_track(c, tq[k]);
-    }
-    std::stable_partition(dev.begin(), dev.end(), [](const DepTrack& d) { return d.ux == 0.0 && d.uy == 0.0; });
-    int64_t npar = 0;
-    while (npar < n && dev[npar].ux == 0.0 && dev[npar].uy == 0.0) ++npar;
-    if (n) HIP_TRY(hipMemcpyAsync(ws + L.off_tracks, dev.data(), n * sizeof(DepTrack), hipMemcpyHostToDevice, stream));
+    DepTrack* dev = all_tracks.data() + track_offsets[q];
+    for (int64_t k = 0; k < n; ++k) dev[k] = prepare_track(c, tq[k]);
+    // parallel tracks first, as the kernel expects
+    const int64_t npar =
+        std::stable_partition(dev, dev + n, [](const DepTrack& d) { return d.ux == 0.0 && d.uy == 0.0; }) - dev;
 
     const Coef cp = species_coef(c, dts[q], 0), cn = species_coef(c, dts[q], 1);
     const double dz = c->gap / c->nz, dV = c->dx * c->dy * dz;
     const Tiling ts = sec.R ? section_tiling(*c, zc_run) : batch_tiling(*c, T, R, rows, exec, tile_x, zc_run);
-    const Tiling td = deposit_tiling(c->nx, c->ny, c->nz);
     BatchInstance& bi = table[q];
     for (int par = 0; par < 2; ++par) {
       StepParams& sp = bi.sp[par];
@@ -1527,7 +1522,6 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
       sp.step0 = 0;
       sp.min_stop_step = train ? INT64_MAX : 0;  // a pulse train ends with its last period
       sp.partials = (double*)(ws + L.off_partials) + (size_t)par * L.slots * kAcc * T;
-      sp.counter = (unsigned*)(ws + L.off_counter);
       sp.state = states + q;
       sp.trace = nullptr;
     }
@@ -1559,27 +1553,36 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
         }
       }
     }
-    HIP_TRY(hipMemcpyAsync(states + q, &init, sizeof(init), hipMemcpyHostToDevice, stream));
-    if (n || c->uniform_n0 > 0.0) {
-      DepositParams dp = base_deposit(c, dts[q], td);
-      dp.pos = (double*)(ws + L.off_field[0]);
-      dp.neg = (double*)(ws + L.off_field[1]);
-      dp.uniform = c->uniform_n0;
-      dp.par = (const DepTrack*)(ws + L.off_tracks);
-      dp.npar = (int)npar;
-      dp.tilt = (const DepTrack*)(ws + L.off_tracks) + npar;
-      dp.ntilt = (int)(n - npar);
-      dp.same_radii = same_radii(tq, n);
-      dp.partials = (double*)(ws + L.off_partials);
-      dp.counter = (unsigned*)(ws + L.off_counter);
-      dp.state = states + q;
-      HIP_TRY(launch_deposit(dp, stream));
-    }
-    if (train)  // the first pulse's densities (the fields held zero before it)
-      for (int f = 0; f < 2; ++f)
-        HIP_TRY(hipMemcpyAsync(ws + L.off_pulse[f], ws + L.off_field[f], L.field_elems * sizeof(double),
-                               hipMemcpyDeviceToDevice, stream));
+    init_states[q] = init;
+    // the first pulse's deposit (of nothing, if there is none) writes the fields
+    DepositParams& dp = deposits[q];
+    dp = base_deposit(c, dts[q], ninst);
+    dp.fresh = 1;
+    dp.pos = (double*)(ws + L.off_field[0]);
+    dp.neg = (double*)(ws + L.off_field[1]);
+    dp.pos2 = (double*)(ws + L.off_field[2]);
+    dp.neg2 = (double*)(ws + L.off_field[3]);
+    dp.pulse_pos = train ? (double*)(ws + L.off_pulse[0]) : nullptr;
+    dp.pulse_neg = train ? (double*)(ws + L.off_pulse[1]) : nullptr;
+    dp.uniform = c->uniform_n0;
+    dp.par = (const DepTrack*)(ws + B.off_tracks) + track_offsets[q];
+    dp.npar = (int)npar;
+    dp.tilt = dp.par + npar;
+    dp.ntilt = (int)(n - npar);
+    dp.same_radii = same_radii(tq, n);
+    dp.partials = (double*)(ws + L.off_partials);
+    dp.state = states + q;
+    dp.tile_begin = deposit_tiles;
+    deposit_tiles += dp.ntiles;
   }
+  static_assert(sizeof(DepositParams) <= sizeof(BatchInstance), "the deposit table lies where the step table will");
+  if (!all_tracks.empty())
+    HIP_TRY(hipMemcpyAsync(ws + B.off_tracks, all_tracks.data(), all_tracks.size() * sizeof(DepTrack),
+                           hipMemcpyHostToDevice, stream));
+  HIP_TRY(hipMemcpyAsync(states, init_states.data(), ninst * sizeof(RunState), hipMemcpyHostToDevice, stream));
+  HIP_TRY(hipMemcpyAsync(ws + B.off_table, deposits.data(), ninst * sizeof(DepositParams), hipMemcpyHostToDevice,
+                         stream));
+  HIP_TRY(launch_deposit_batch((const DepositParams*)(ws + B.off_table), ninst, deposit_tiles, stream));
   // The pass chain runs on the tile list of the running instances only: the
   // table is rebuilt (and the graph re-captured) whenever a quarter of its
   // instances have stopped, so finished chambers cost no dispatches.  All
@@ -1744,27 +1747,33 @@ int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* e
   char* ws = (char*)d_workspace;
   const size_t plane = (size_t)ch->nx * ch->ny * sizeof(double);
   const size_t bytes = L.field_elems * sizeof(double);
-  HIP_TRY(hipMemcpyAsync(ws + L.off_field[0], d_pos, bytes, hipMemcpyDeviceToDevice, stream));
-  HIP_TRY(hipMemcpyAsync(ws + L.off_field[1], d_neg, bytes, hipMemcpyDeviceToDevice, stream));
-  for (int f = 0; f < 2; ++f) {  // electrode planes of the input pair are zero by definition
-    HIP_TRY(hipMemsetAsync(ws + L.off_field[f], 0, plane, stream));
-    HIP_TRY(hipMemsetAsync(ws + L.off_field[f] + (size_t)ch->nz * plane, 0, plane, stream));
+  // the caller's arrays are the first field pair (copied into the workspace if
+  // they are not aligned for every kernel)
+  double* first[2] = {d_pos, d_neg};
+  const bool own = (uintptr_t)d_pos % 16 || (uintptr_t)d_neg % 16;
+  for (int f = 0; f < 2; ++f) {
+    if (own) {
+      first[f] = (double*)(ws + L.off_field[f]);
+      HIP_TRY(hipMemcpyAsync(first[f], f ? d_neg : d_pos, bytes, hipMemcpyDeviceToDevice, stream));
+    }
+    // electrode planes are zero by definition, in both pairs
+    HIP_TRY(hipMemset2DAsync(first[f], (size_t)ch->nz * plane, 0, plane, 2, stream));
+    HIP_TRY(hipMemset2DAsync(ws + L.off_field[2 + f], (size_t)ch->nz * plane, 0, plane, 2, stream));
   }
-  for (int f = 2; f < 4; ++f) HIP_TRY(hipMemsetAsync(ws + L.off_field[f], 0, bytes, stream));
-  HIP_TRY(hipMemsetAsync(ws + L.off_counter, 0, 64 * sizeof(unsigned), stream));
   const RunState init = initial_run_state();
   HIP_TRY(hipMemcpyAsync(ws + L.off_state, &init, sizeof(init), hipMemcpyHostToDevice, stream));
   std::vector<Event> none;
-  std::vector<DepTrack> nodev;
   RunState fin;
   int issued = 0;
   HostSlots hs;
   host_slots(exec, 1, hs);
-  rc = run_loop(ch, dt, exec, ws, L, none, nodev, 1, nsteps, INT64_MAX, 0.0, T, stream, hs, &fin, &issued);
+  rc = run_loop(ch, dt, exec, ws, L, first[0], first[1], none, 1, nsteps, INT64_MAX, 0.0, T, stream, hs, &fin, &issued);
   if (rc) return rc;
-  const int last = fin.passes & 1;
-  HIP_TRY(hipMemcpyAsync(d_pos, ws + L.off_field[2 * last], bytes, hipMemcpyDeviceToDevice, stream));
-  HIP_TRY(hipMemcpyAsync(d_neg, ws + L.off_field[2 * last + 1], bytes, hipMemcpyDeviceToDevice, stream));
+  const double* last[2] = {first[0], first[1]};
+  if (fin.passes & 1)
+    for (int f = 0; f < 2; ++f) last[f] = (const double*)(ws + L.off_field[2 + f]);
+  if (last[0] != d_pos) HIP_TRY(hipMemcpyAsync(d_pos, last[0], bytes, hipMemcpyDeviceToDevice, stream));
+  if (last[1] != d_neg) HIP_TRY(hipMemcpyAsync(d_neg, last[1], bytes, hipMemcpyDeviceToDevice, stream));
   if (h_trace)
     HIP_TRY(hipMemcpyAsync(h_trace, ws + L.off_trace, (size_t)nsteps * IT_TRACE_COLS * sizeof(double),
                            hipMemcpyDeviceToHost, stream));
