@@ -36,7 +36,8 @@ constexpr int kH = 128, kIn = 6;
 constexpr int oW1 = 0, ob1 = oW1 + kH * kIn, oW2 = ob1 + kH, ob2 = oW2 + kH * kH, oW3 = ob2 + kH,
               ob3 = oW3 + kH * kH, ow4 = ob3 + kH, ob4 = ow4 + kH, kP = ob4 + 1;  // 34049
 constexpr int kPpad = (kP + 63) / 64 * 64;
-constexpr int kTileS = 64;       // samples per forward block (4 waves x 16)
+constexpr int kTileS = 64;       // samples per query tile, and per BF16 forward tile
+constexpr int64_t kFewQueries = 8192;
 constexpr int kActStride = kH + 4;  // padded BF16 row (avoids LDS bank conflicts)
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
@@ -86,6 +87,13 @@ Model carve_model(void* base, int M) {
   return md;
 }
 
+// The BF16 weights of a model of M members (for kernels that learn M from the
+// header).
+__device__ inline const unsigned short* bf16_weights(const Model& md, int M) {
+  const size_t field = ((size_t)M * kP * sizeof(float) + 255) / 256 * 256;
+  return (const unsigned short*)((const char*)md.master + 3 * field);
+}
+
 struct TrainWs {  // per member: [M][n][...]
   float *z, *a1, *a2, *a3, *h1, *h2, *h3, *y, *dy, *d1, *d2, *d3, *grad, *loss, *base;
 };
@@ -128,8 +136,7 @@ TrainWs carve_train(void* base, int M, int64_t n) {
 // (y1/y2) int_0^{ln(1 + ln(1+y2)/y1)} exp(y1 (e^w - 1)) dw (no overflow for
 // large y1), y1 = 8 pi D/(alpha N0), y2 = 2 d D/(mu b^2 E), N0 = LET/W, and
 // f_B = ln(1+u)/u with u = alpha/(mu+ + mu-) n0 d^2/V.  The quadrature is
-// summed in four parts of kGL/4 nodes (added in order), so that four
-// threads can share a query.
+// summed in four parts of kGL/4 nodes (added in order).
 struct BaseArgs {
   double y1, y2, upper;
 };
@@ -145,9 +152,11 @@ __device__ inline BaseArgs base_args(const Header& H, const float* x) {
   return a;
 }
 
-__device__ inline double base_part(const Header& H, const BaseArgs& a, int part) {
+// Part `part` of the weighted sum, of `parts` equal ones.
+__device__ inline double base_part(const Header& H, const BaseArgs& a, int part, int parts) {
+  const int len = kGL / parts;
   double s = 0.0;
-  for (int q = part * (kGL / 4); q < (part + 1) * (kGL / 4); ++q) {
+  for (int q = part * len; q < (part + 1) * len; ++q) {
     const double w = 0.5 * a.upper * (H.gl_x[q] + 1.0);
     s += H.gl_w[q] * exp(a.y1 * expm1(w));
   }
@@ -164,25 +173,34 @@ __device__ inline double base_finish(const Header& H, const float* x, const Base
 
 __device__ double baseline(const Header& H, const float* x) {
   const BaseArgs a = base_args(H, x);
-  const double p0 = base_part(H, a, 0), p1 = base_part(H, a, 1), p2 = base_part(H, a, 2), p3 = base_part(H, a, 3);
-  return base_finish(H, x, a, ((p0 + p1) + p2) + p3);
+  double s = base_part(H, a, 0, 4);
+  for (int p = 1; p < 4; ++p) s += base_part(H, a, p, 4);
+  return base_finish(H, x, a, s);
 }
 
-// Baseline of the 64 samples of a tile with all 256 threads: wave p sums
-// quadrature part p of sample s0 + lane into part[p][lane]; after a barrier
-// thread s < 64 calls base_of.
+// Baseline of the S samples of a tile: the block's 256 threads share the
+// quadratures (an exponential of FP64 takes as long as dozens of the network's
+// instructions), thread p S + s sums part p of sample s0 + s into part[p][s];
+// after a barrier thread s < S calls base_of, which adds its sample's parts.
+template <int S>
+constexpr int kBaseParts = 256 / S;
+
+template <int S>
 __device__ inline void base_parts(const Header& H, const float* __restrict__ X, int64_t n, int64_t s0,
-                                  double (*part)[kTileS]) {
-  const int p = threadIdx.x / 64, s = threadIdx.x % 64;
+                                  double (*part)[S]) {
+  const int p = threadIdx.x / S, s = threadIdx.x % S;
   const int64_t gs = s0 + s;
-  part[p][s] = H.use_baseline && gs < n ? base_part(H, base_args(H, X + gs * kIn), p) : 0.0;
+  if (H.use_baseline && gs < n) part[p][s] = base_part(H, base_args(H, X + gs * kIn), p, kBaseParts<S>);
 }
 
-__device__ inline double base_of(const Header& H, const float* __restrict__ X, int64_t gs,
-                                 const double (*part)[kTileS], int s) {
+template <int S>
+__device__ inline double base_of(const Header& H, const float* __restrict__ X, int64_t gs, const double (*part)[S],
+                                 int s) {
   if (!H.use_baseline) return 0.0;
   const float* x = X + gs * kIn;
-  return base_finish(H, x, base_args(H, x), ((part[0][s] + part[1][s]) + part[2][s]) + part[3][s]);
+  double sum = part[0][s];
+  for (int p = 1; p < kBaseParts<S>; ++p) sum += part[p][s];
+  return base_finish(H, x, base_args(H, x), sum);
 }
 
 __device__ inline unsigned short to_bf16(float f) {  // round to nearest even
@@ -210,397 +228,250 @@ struct ForwardOut {  // optional stores of the training forward (member slices)
 };
 
 // ---------------------------------------------------------------------------
-// FP32 models.  Every kernel runs 256 threads on a tile of 64 samples of one
-// member; wave w owns samples 16w..16w+15 of the tile.  The training kernel
-// stages the 128 x 128 weights of a layer in LDS (wl[o][i], rows padded to
-// kWS), read from global memory into registers one layer ahead (64 values
-// per thread, element tid + 256 u of the matrix), so that their latency
-// hides behind the previous layer; the query kernel stages them in halves
-// (forward_query_f32).  Products run on v_mfma_f32_16x16x4f32 (A[i][k]: lane
-// i + 16 k, B[k][j]: lane j + 16 k, D[i][j]: lane j + 16 (i/4), item i % 4),
-// four 16-wide output tiles per pass sharing the A operand, k taken 4 at a
-// time in increasing order.  Every per-element value a thread computes sits
-// at (sample 16w + 4 (lane/16) + v, unit 16 t + lane % 16), v = 0..3, t =
-// 0..7, the D layout, in every layer: so the pre-activations a thread
-// stores in the forward pass are read back, in the backward pass, by that
-// same thread.
-constexpr int kWS = kH + 4;
+// FP32 models.  A block of 256 threads takes a tile of S samples of one
+// member; wave w computes units 32 w .. 32 w + 31 of every sample of the tile,
+// so each wave reads its own part of a layer's weights, straight from the L2
+// into registers one layer ahead, and only the activations go through LDS.
+// Products run on v_mfma_f32_16x16x4f32 (A[i][k]: lane i + 16 k, B[k][j]: lane
+// j + 16 k, D[i][j]: lane j + 16 (i/4), item i % 4).  Which four of the 128
+// terms a product takes is free as long as A and B agree: product e takes
+// terms 32 q + e, q = lane / 16, so that a lane's terms are consecutive in
+// memory and in LDS (16-byte loads).  Column j of output tile t is unit
+// 32 w + 2 j + t, so a thread's two units of a sample are neighbours.  Every
+// per-element value a thread computes sits at (sample 16 st + 4 (lane/16) + v,
+// unit 32 w + 2 (lane % 16) + t) in every layer, so the pre-activations stay in
+// its registers for the backward pass.
+//
+// What bounds it: the FP32 matrix instructions (32 cycles each) where the
+// tiles fill the chip (half of their peak with 65 536 queries: 219 us, 233 with
+// the weights staged in LDS), the latency of a tile's chain of layers where
+// they do not (100 queries 32 us, 68 in tiles of 64; 2048 samples of four
+// members, a training tile per CU, 28 us, 51 with 64 samples on half of the
+// CUs).
+typedef float float4u_t __attribute__((ext_vector_type(4), aligned(4)));  // parameters are not aligned further
+typedef float float2u_t __attribute__((ext_vector_type(2), aligned(4)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
 
-// The small parameters of a member (W1 and b1, b2, b3, w4, b4), staged in
-// LDS once per tile: three contiguous runs of the parameter vector.
+// A wave's part of a 128 x 128 layer: term 32 q + e of tiles t = 0, 1.
+struct WFrag {
+  float v[2][32];
+};
+
+// Forward: B[k][j] = W[unit][k].
+__device__ inline void wload_fwd(WFrag& f, const float* __restrict__ W) {
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const float* row = W + (32 * wave + 2 * (lane & 15) + t) * kH + 32 * (lane >> 4);
+#pragma unroll
+    for (int e = 0; e < 32; e += 4) {
+      const float4u_t x = *(const float4u_t*)(row + e);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) f.v[t][e + c] = x[c];
+    }
+  }
+}
+
+// Backward: B[k][j] = W[k][unit].
+__device__ inline void wload_bwd(WFrag& f, const float* __restrict__ W) {
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const float* col = W + 32 * (lane >> 4) * kH + 32 * wave + 2 * (lane & 15);
+#pragma unroll
+  for (int e = 0; e < 32; ++e) {
+    const float2u_t x = *(const float2u_t*)(col + e * kH);
+    f.v[0][e] = x[0];
+    f.v[1][e] = x[1];
+  }
+}
+
+// acc[st][t]: the products of the tile's activations with the wave's weights.
+template <int S>
+__device__ inline void mm_f32(const float (*in)[kActStride], const WFrag& f, float4_t (&acc)[S / 16][2]) {
+  const int lane = threadIdx.x % 64;
+#pragma unroll
+  for (int st = 0; st < S / 16; ++st)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[st][t] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int e = 0; e < 32; e += 4) {
+    float4_t a[S / 16];
+#pragma unroll
+    for (int st = 0; st < S / 16; ++st) a[st] = *(const float4_t*)&in[16 * st + (lane & 15)][32 * (lane >> 4) + e];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int st = 0; st < S / 16; ++st)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          acc[st][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[st][c], f.v[t][e + c], acc[st][t], 0, 0, 0);
+  }
+}
+
+// Calls f(st, v, s) for the samples s of the tile that this thread's values
+// belong to.
+template <int S, class F>
+__device__ inline void each_sample(F f) {
+  const int lane = threadIdx.x % 64;
+#pragma unroll
+  for (int st = 0; st < S / 16; ++st)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f(st, v, 16 * st + 4 * (lane >> 4) + v);
+}
+
+// The first unit of this thread (the second is the next).
+__device__ inline int unit0() { return 32 * (int)(threadIdx.x / 64) + 2 * (int)(threadIdx.x & 15); }
+
+// Standardised inputs of the tile.
+template <int S>
+__device__ inline void inputs_f32(const Header& H, const float* __restrict__ X, int64_t n, int64_t s0, float* zs) {
+  for (int q = threadIdx.x; q < S * kIn; q += 256) {
+    const int64_t gs = s0 + q / kIn;
+    const int i = q % kIn;
+    zs[q] = gs < n ? (logf(X[gs * kIn + i]) - H.mu[i]) / H.sigma[i] : 0.0f;
+  }
+}
+
+// A thread's parameters outside the 128 x 128 matrices.
 struct SmallP {
-  float w1b1[kH * kIn + kH];  // W1 [128][6], then b1
-  float b2[kH];
-  float b3w4b4[2 * kH + 1];   // b3, w4, b4
+  float w1[2][kIn], b1[2], b2[2], b3[2];
 };
 
 __device__ inline void sload(const float* __restrict__ master, SmallP& sp) {
-  const int tid = threadIdx.x;
+  const int o = unit0();
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int q = tid + 256 * u;
-    if (q < kH * kIn + kH) sp.w1b1[q] = master[oW1 + q];
-  }
-  if (tid < kH) sp.b2[tid] = master[ob2 + tid];
+  for (int t = 0; t < 2; ++t) {
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int q = tid + 256 * u;
-    if (q < 2 * kH + 1) sp.b3w4b4[q] = master[ob3 + q];
+    for (int i = 0; i < kIn; ++i) sp.w1[t][i] = master[oW1 + (o + t) * kIn + i];
+    sp.b1[t] = master[ob1 + o + t];
+    sp.b2[t] = master[ob2 + o + t];
+    sp.b3[t] = master[ob3 + o + t];
   }
 }
 
-struct WRegs {
-  float v[64];
-};
-
-__device__ inline void wload(WRegs& r, const float* __restrict__ W) {
+// Pre-activation of the first layer of sample s, unit t.
+__device__ inline float first_layer(const SmallP& sp, const float* zs, int s, int t) {
+  float a = sp.b1[t];
 #pragma unroll
-  for (int u = 0; u < 64; ++u) r.v[u] = W[threadIdx.x + 256 * u];
+  for (int i = 0; i < kIn; ++i) a += sp.w1[t][i] * zs[s * kIn + i];
+  return a;
 }
 
-__device__ inline void wstore(const WRegs& r, float (*wl)[kWS]) {
-#pragma unroll
-  for (int u = 0; u < 64; ++u) {
-    const int q = threadIdx.x + 256 * u;
-    wl[q / kH][q % kH] = r.v[u];
-  }
-}
-
-// acc[u] += in[16w + i][k] * B[k][16 (t0 + u) + j] over k = 0..127, with
-// B[k][j] = wl[j][k] (forward: out = in W^T) or wl[k][j] (backward:
-// out = in W).
-template <bool BWD>
-__device__ inline void mfma_pass(const float (*in)[kActStride], const float (*wl)[kWS], int t0, float4_t* acc) {
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int arow = wave * 16 + (lane & 15), kq = lane >> 4, j = lane & 15;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) acc[u] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 8
-  for (int kk = 0; kk < kH / 4; ++kk) {
-    const int k = 4 * kk + kq;
-    const float a = in[arow][k];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = (t0 + u) * 16 + j;
-      acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, BWD ? wl[k][c] : wl[c][k], acc[u], 0, 0, 0);
-    }
-  }
-}
-
-// Hidden layer 2 or 3 of the training forward pass: out = silu(in W^T + b),
-// with stores of the pre-activations and activations.  Ends with a barrier.
-__device__ void layer_fwd_f32(const float (*in)[kActStride], float (*out)[kActStride], const float (*wl)[kWS],
-                              const float* __restrict__ bias, int64_t n, int64_t s0, float* sa, float* sh) {
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-#pragma unroll 1
-  for (int t0 = 0; t0 < kH / 16; t0 += 4) {
-    float4_t acc[4];
-    mfma_pass<false>(in, wl, t0, acc);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int o = (t0 + u) * 16 + (lane & 15);
-      const float b = bias[o];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int s = wave * 16 + 4 * (lane >> 4) + v;
-        const float a = acc[u][v] + b;
-        const float h = silu(a);
-        out[s][o] = h;
-        const int64_t gs = s0 + s;
-        if (gs < n) {
-          sa[gs * kH + o] = a;
-          sh[gs * kH + o] = h;
-        }
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Backward through a hidden layer: dprev = (d W) * silu'(a_prev), where
-// a_prev are the pre-activations this thread stored in the forward pass
-// (read before the pass's products, so that the loads overlap them).
-// Optional LDS copy (the next layer's input); stores for the weight
-// gradients.  Ends with a barrier.
-__device__ void layer_bwd_f32(const float (*d)[kActStride], float (*dout)[kActStride], const float (*wl)[kWS],
-                              const float* apre, int64_t n, int64_t s0, float* dstore) {
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-#pragma unroll 1
-  for (int t0 = 0; t0 < kH / 16; t0 += 4) {
-    float ap[4][4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t gs = s0 + wave * 16 + 4 * (lane >> 4) + v;
-        ap[u][v] = gs < n ? apre[gs * kH + (t0 + u) * 16 + (lane & 15)] : 0.0f;
-      }
-    float4_t acc[4];
-    mfma_pass<true>(d, wl, t0, acc);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int o = (t0 + u) * 16 + (lane & 15);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int s = wave * 16 + 4 * (lane >> 4) + v;
-        const int64_t gs = s0 + s;
-        float dv = 0.0f;
-        if (gs < n) {
-          dv = acc[u][v] * dsilu(ap[u][v]);
-          dstore[gs * kH + o] = dv;
-        }
-        if (dout) dout[s][o] = dv;
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Training forward pass of one FP32 member over samples [s0, s0 + 64),
-// storing what the backward pass and the weight gradients read.  On entry
-// `pf` holds (or is loading) this member's W2; on return it is loading
-// `next` (when not null).  Leaves the standardised outputs in ys[64] and h3
-// in act[0].
-__device__ void forward_tile_f32(const Header& H, const float* __restrict__ master, const float* __restrict__ X,
-                                 int64_t n, int64_t s0, float* zs, float (*act)[kTileS][kActStride],
-                                 float (*wl)[kWS], SmallP& sp, float (*yp)[kTileS], float* ys, WRegs& pf,
-                                 const float* next, const ForwardOut& st) {
-  const int tid = threadIdx.x;
-  const int wave = tid / 64, lane = tid % 64;
-  sload(master, sp);  // its last readers passed a barrier
-  // standardised inputs
-  for (int q = tid; q < kTileS * kIn; q += 256) {
-    const int s = q / kIn, i = q % kIn;
-    const int64_t gs = s0 + s;
-    float zv = 0.0f;
-    if (gs < n) zv = (logf(X[gs * kIn + i]) - H.mu[i]) / H.sigma[i];
-    zs[q] = zv;
-    if (gs < n) st.z[gs * kIn + i] = zv;
-  }
-  __syncthreads();
-  // layer 1 (FP32 FMAs, D layout)
-#pragma unroll 2
-  for (int t = 0; t < kH / 16; ++t) {
-    const int o = t * 16 + (lane & 15);
-    float w1[kIn];
-#pragma unroll
-    for (int i = 0; i < kIn; ++i) w1[i] = sp.w1b1[o * kIn + i];
-    const float b = sp.w1b1[kH * kIn + o];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int s = wave * 16 + 4 * (lane >> 4) + v;
-      float a = b;
-#pragma unroll
-      for (int i = 0; i < kIn; ++i) a += w1[i] * zs[s * kIn + i];
-      const float h = silu(a);
-      act[0][s][o] = h;
-      const int64_t gs = s0 + s;
-      if (gs < n) {
-        st.a1[gs * kH + o] = a;
-        st.h1[gs * kH + o] = h;
-      }
-    }
-  }
-  wstore(pf, wl);  // W2 (wl's last readers passed a barrier)
-  __syncthreads();
-  wload(pf, master + oW3);
-  layer_fwd_f32(act[0], act[1], wl, sp.b2, n, s0, st.a2, st.h2);
-  wstore(pf, wl);  // W3
-  __syncthreads();
-  if (next) wload(pf, next);
-  layer_fwd_f32(act[1], act[0], wl, sp.b3w4b4, n, s0, st.a3, st.h3);
-  // output layer: four partial dot products of 32 terms per sample
-  {
-    const int s = lane, p = wave;
+// Output layer: four partial dot products of 32 terms per sample, into
+// yp[p][s]; w4 (128 values, then b4) in LDS.  The sum is output_f32's.
+template <int S>
+__device__ inline void dots_f32(const float (*act)[kActStride], const float* w4, float (*yp)[S]) {
+  const int s = threadIdx.x % S, p = threadIdx.x / S;
+  if (p < 4) {
     float y = 0.0f;
 #pragma unroll 8
-    for (int i = 32 * p; i < 32 * p + 32; ++i) y += sp.b3w4b4[kH + i] * act[0][s][i];
+    for (int i = 32 * p; i < 32 * p + 32; ++i) y += w4[i] * act[s][i];
     yp[p][s] = y;
   }
-  __syncthreads();
-  if (tid < kTileS) {
-    const float y = sp.b3w4b4[2 * kH] + (((yp[0][tid] + yp[1][tid]) + yp[2][tid]) + yp[3][tid]);
-    ys[tid] = y;
-    const int64_t gs = s0 + tid;
-    if (gs < n) st.y[gs] = y;
-  }
-  __syncthreads();
 }
 
-// Query form of the FP32 forward pass, sized for two blocks per CU (78 KB of
-// LDS): one activation buffer, updated in place (every wave reads and writes
-// only its own 16 rows, so a layer's two passes keep their results in
-// registers until both have read the input), and each 128 x 128 matrix
-// staged in two halves of 64 output rows, one per pass (32 values per
-// thread in flight, element tid + 256 u of the half).  Every output is summed
-// in the same order as in forward_tile_f32, so both give the same values.
-struct WHalf {
-  float v[32];
-};
-
-__device__ inline void wload_half(WHalf& r, const float* __restrict__ W, int half) {
-#pragma unroll
-  for (int u = 0; u < 32; ++u) r.v[u] = W[half * 64 * kH + threadIdx.x + 256 * u];
+template <int S>
+__device__ inline float output_f32(const float* w4, const float (*yp)[S], int s) {
+  return w4[kH] + (((yp[0][s] + yp[1][s]) + yp[2][s]) + yp[3][s]);
 }
 
-__device__ inline void wstore_half(const WHalf& r, float (*wl)[kWS]) {
-#pragma unroll
-  for (int u = 0; u < 32; ++u) {
-    const int q = threadIdx.x + 256 * u;
-    wl[q / kH][q % kH] = r.v[u];
-  }
-}
+// One FP32 training step's per-sample work for a tile of samples of one
+// member: the forward pass, the loss gradient dy = 2 (y - t_std) / n, and the
+// pre-activation gradients of the three hidden layers; activations and
+// gradients go out for the weight gradients.  The baseline of each sample is
+// written by the member-0 blocks (the loss kernel reads it).  Tiles of 32
+// samples: a minibatch of 2048 of four members then puts a block on every CU.
+constexpr int kTrainS = 32;
 
-// One hidden layer of the query form: act = silu(act W^T + b).  On entry pf
-// holds half 0 of W and wl is free (its last readers passed a barrier); on
-// return pf is loading half 0 of `next` (when not null).  Ends with a
-// barrier.
-__device__ void layer_query_f32(float (*act)[kActStride], float (*wl)[kWS], const float* bias,
-                                const float* __restrict__ W, WHalf& pf, const float* next) {
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  float4_t acc[2][4];
-  wstore_half(pf, wl);
-  __syncthreads();
-  wload_half(pf, W, 1);
-  mfma_pass<false>(act, wl, 0, acc[0]);
-  __syncthreads();  // every wave is done with half 0
-  wstore_half(pf, wl);
-  __syncthreads();
-  if (next) wload_half(pf, next, 0);
-  mfma_pass<false>(act, wl, 0, acc[1]);
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int o = h * 64 + u * 16 + (lane & 15);
-      const float b = bias[o];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) act[wave * 16 + 4 * (lane >> 4) + v][o] = silu(acc[h][u][v] + b);
-    }
-  __syncthreads();
-}
-
-// Query forward pass of one FP32 member over samples [s0, s0 + 64): pf holds
-// (or is loading) half 0 of this member's W2 on entry and is loading `next`
-// on return.  Leaves the standardised outputs in ys[64].
-__device__ void forward_query_f32(const Header& H, const float* __restrict__ master, const float* __restrict__ X,
-                                  int64_t n, int64_t s0, float* zs, float (*act)[kActStride], float (*wl)[kWS],
-                                  SmallP& sp, float (*yp)[kTileS], float* ys, WHalf& pf, const float* next) {
-  const int tid = threadIdx.x;
-  const int wave = tid / 64, lane = tid % 64;
-  sload(master, sp);  // its last readers passed a barrier
-  for (int q = tid; q < kTileS * kIn; q += 256) {
-    const int s = q / kIn, i = q % kIn;
-    const int64_t gs = s0 + s;
-    zs[q] = gs < n ? (logf(X[gs * kIn + i]) - H.mu[i]) / H.sigma[i] : 0.0f;
-  }
-  __syncthreads();
-#pragma unroll 2
-  for (int t = 0; t < kH / 16; ++t) {
-    const int o = t * 16 + (lane & 15);
-    float w1[kIn];
-#pragma unroll
-    for (int i = 0; i < kIn; ++i) w1[i] = sp.w1b1[o * kIn + i];
-    const float b = sp.w1b1[kH * kIn + o];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int s = wave * 16 + 4 * (lane >> 4) + v;
-      float a = b;
-#pragma unroll
-      for (int i = 0; i < kIn; ++i) a += w1[i] * zs[s * kIn + i];
-      act[s][o] = silu(a);
-    }
-  }
-  layer_query_f32(act, wl, sp.b2, master + oW2, pf, master + oW3);
-  layer_query_f32(act, wl, sp.b3w4b4, master + oW3, pf, next);
-  {
-    const int s = lane, p = wave;
-    float y = 0.0f;
-#pragma unroll 8
-    for (int i = 32 * p; i < 32 * p + 32; ++i) y += sp.b3w4b4[kH + i] * act[s][i];
-    yp[p][s] = y;
-  }
-  __syncthreads();
-  if (tid < kTileS) ys[tid] = sp.b3w4b4[2 * kH] + (((yp[0][tid] + yp[1][tid]) + yp[2][tid]) + yp[3][tid]);
-  __syncthreads();
-}
-
-// One FP32 training step's per-sample work for a tile of 64 samples of one
-// member: the forward pass (storing what the weight gradients need), the
-// loss gradient dy = 2 (y - t_std) / n, and the pre-activation gradients of
-// the three hidden layers.  The baseline of each sample is written by the
-// member-0 blocks (the loss kernel reads it).
-__global__ __launch_bounds__(256) void train_tile_f32_kernel(Model md, const float* __restrict__ X,
-                                                             const float* __restrict__ t, int64_t n, TrainWs ws) {
-  __shared__ float zs[kTileS * kIn];
-  __shared__ float act[2][kTileS][kActStride];
-  __shared__ float wl[kH][kWS];
-  __shared__ SmallP sp;
-  __shared__ float yp[4][kTileS];
-  __shared__ float ys[kTileS], dys[kTileS];
-  __shared__ double bp[4][kTileS];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void train_tile_f32_kernel(
+    Model md, const float* __restrict__ X, const float* __restrict__ t_, int64_t n, TrainWs ws) {
+  constexpr int S = kTrainS, NS = S / 16;
+  __shared__ float zs[S * kIn];
+  __shared__ __align__(16) float act[2][S][kActStride];
+  __shared__ float w4[kH + 1];
+  __shared__ float yp[4][S];
+  __shared__ float dys[S];
+  __shared__ double bp[kBaseParts<S>][S];
   const Header& H = *md.hdr;
   const int tid = threadIdx.x;
-  const int wave = tid / 64, lane = tid % 64;
   const int m = blockIdx.y;
-  const int64_t s0 = (int64_t)blockIdx.x * kTileS;
+  const int64_t s0 = (int64_t)blockIdx.x * S;
   const float* master = md.master + (size_t)m * kP;
   const size_t nh = (size_t)n * kH;
-  const ForwardOut st{ws.z + (size_t)m * n * kIn, ws.a1 + m * nh, ws.a2 + m * nh, ws.a3 + m * nh,
-                      ws.h1 + m * nh, ws.h2 + m * nh, ws.h3 + m * nh, ws.y + (size_t)m * n};
-  WRegs pf;
-  wload(pf, master + oW2);
+  const int o = unit0();
+  WFrag fa, fb;
+  SmallP sp;
+  wload_fwd(fa, master + oW2);
+  sload(master, sp);
+  if (tid < kH + 1) w4[tid] = master[ow4 + tid];
+  inputs_f32<S>(H, X, n, s0, zs);
   // the baseline and target of each sample, while W2 is on its way
-  base_parts(H, X, n, s0, bp);
+  base_parts<S>(H, X, n, s0, bp);
   __syncthreads();
   const int64_t gt = s0 + tid;
   float ty = 0.0f;
-  if (tid < kTileS && gt < n) {
-    const float base = (float)base_of(H, X, gt, bp, tid);
+  if (tid < S && gt < n) {
+    const float base = (float)base_of<S>(H, X, gt, bp, tid);
     if (m == 0) ws.base[gt] = base;
-    ty = (t[gt] - base - H.t_mu) / H.t_sigma;
+    ty = (t_[gt] - base - H.t_mu) / H.t_sigma;
   }
-  forward_tile_f32(H, master, X, n, s0, zs, act, wl, sp, yp, ys, pf, master + oW2, st);
-  if (tid < kTileS) {
+  if (tid < S * kIn && s0 + tid / kIn < n) ws.z[(size_t)m * n * kIn + s0 * kIn + tid] = zs[tid];
+  // a pair of values of sample s: into LDS and, for real samples, to memory
+  auto put = [&](float (*to)[kActStride], float* mem, int s, float x, float y) {
+    if (to) *(float2_t*)&to[s][o] = float2_t{x, y};
+    if (s0 + s < n) *(float2_t*)(mem + (size_t)m * nh + (s0 + s) * kH + o) = float2_t{x, y};
+  };
+  float a1[NS][4][2], a2[NS][4][2], a3[NS][4][2];
+  each_sample<S>([&](int st, int v, int s) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) a1[st][v][t] = first_layer(sp, zs, s, t);
+    put(act[0], ws.h1, s, silu(a1[st][v][0]), silu(a1[st][v][1]));
+  });
+  __syncthreads();
+  float4_t acc[NS][2];
+  wload_fwd(fb, master + oW3);
+  mm_f32<S>(act[0], fa, acc);
+  each_sample<S>([&](int st, int v, int s) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) a2[st][v][t] = acc[st][t][v] + sp.b2[t];
+    put(act[1], ws.h2, s, silu(a2[st][v][0]), silu(a2[st][v][1]));
+  });
+  __syncthreads();
+  wload_bwd(fa, master + oW3);
+  mm_f32<S>(act[1], fb, acc);
+  each_sample<S>([&](int st, int v, int s) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) a3[st][v][t] = acc[st][t][v] + sp.b3[t];
+    put(act[0], ws.h3, s, silu(a3[st][v][0]), silu(a3[st][v][1]));
+  });
+  __syncthreads();
+  wload_bwd(fb, master + oW2);
+  dots_f32<S>(act[0], w4, yp);
+  __syncthreads();
+  if (tid < S) {
     float dy = 0.0f;
     if (gt < n) {
-      dy = 2.0f * (ys[tid] - ty) / (float)n;
+      const float y = output_f32<S>(w4, yp, tid);
+      ws.y[(size_t)m * n + gt] = y;
+      dy = 2.0f * (y - ty) / (float)n;
       ws.dy[(size_t)m * n + gt] = dy;
     }
     dys[tid] = dy;
   }
   __syncthreads();
-  // d3 = dy w4 silu'(a3) -> act[1]; the pre-activations are read first
-  float* d3 = ws.d3 + m * nh;
-  float a3[kH / 16][4];
-#pragma unroll
-  for (int tt = 0; tt < kH / 16; ++tt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t gs = s0 + wave * 16 + 4 * (lane >> 4) + v;
-      a3[tt][v] = gs < n ? st.a3[gs * kH + tt * 16 + (lane & 15)] : 0.0f;
-    }
-#pragma unroll
-  for (int tt = 0; tt < kH / 16; ++tt) {
-    const int o = tt * 16 + (lane & 15);
-    const float w4 = sp.b3w4b4[kH + o];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int s = wave * 16 + 4 * (lane >> 4) + v;
-      const int64_t gs = s0 + s;
-      float dv = 0.0f;
-      if (gs < n) {
-        dv = dys[s] * w4 * dsilu(a3[tt][v]);
-        d3[gs * kH + o] = dv;
-      }
-      act[1][s][o] = dv;
-    }
-  }
+  // d3 = dy w4 silu'(a3), then back through the layers: d = (d W) silu'(a)
+  each_sample<S>([&](int st, int v, int s) {
+    put(act[1], ws.d3, s, dys[s] * w4[o] * dsilu(a3[st][v][0]), dys[s] * w4[o + 1] * dsilu(a3[st][v][1]));
+  });
   __syncthreads();
-  layer_bwd_f32(act[1], act[0], wl, st.a2, n, s0, ws.d2 + m * nh);  // wl holds W3
-  wstore(pf, wl);                                                   // W2
+  mm_f32<S>(act[1], fa, acc);
+  each_sample<S>([&](int st, int v, int s) {
+    put(act[0], ws.d2, s, acc[st][0][v] * dsilu(a2[st][v][0]), acc[st][1][v] * dsilu(a2[st][v][1]));
+  });
   __syncthreads();
-  layer_bwd_f32(act[0], nullptr, wl, st.a1, n, s0, ws.d1 + m * nh);
+  mm_f32<S>(act[0], fb, acc);
+  each_sample<S>([&](int st, int v, int s) {
+    put(nullptr, ws.d1, s, acc[st][0][v] * dsilu(a1[st][v][0]), acc[st][1][v] * dsilu(a1[st][v][1]));
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -742,89 +613,175 @@ __global__ __launch_bounds__(128) void delta_bf16_kernel(Model md, const float* 
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradients G[o][i] = sum_s delta[s][o] * in[s][i] (in[s][K] = 1
-// gives the bias) of the four layers, in one launch: block x of the grid
-// walks the jobs' 16 x 16 tiles of (o, i) in turn, block y is the member.
-struct GradJob {
-  const float* delta;  // [n][rows_d]
-  int rows_d;          // width of delta rows (128 or 1)
-  const float* in;     // [n][K]
-  int K;
-  int nO;              // outputs (128 or 1)
-  int w_off, b_off;    // parameter offsets of weights [nO][K] and bias [nO]
-  size_t delta_stride, in_stride;  // member strides
-  int tiles_x, first;  // tiles along i; first block of the job
+// Weight gradients G[o][i] = sum_s delta[s][o] * in[s][i] on FP32 MFMA
+// (v_mfma_f32_16x16x4f32, four samples each).  Slice
+// z takes the samples 16 g + 4 z .. 16 g + 4 z + 3, g = 0, 1, ..., in order, and
+// the four slices' sums are added, in order, where they are used (adam_kernel,
+// sum_grad_kernel): deterministic.  Blocks x < 16 each a 64 x 32 part of a
+// 128 x 128 layer's matrix (a wave 32 outputs by 16 inputs, two tiles that share
+// B; row r of output tile a is unit 2 r + a), blocks 16..18 W1 and b1, b2,
+// b3, and blocks 19..21 w4 and b4, a 16 x 16 tile per wave.  One 16 x 16 tile of all samples per block, as
+// before, read every activation eight times: 29 us for 2048 samples of four
+// members; 17 us now.
+constexpr int kSlices = 4, kMatrixBlocks = 16, kLastBlock = kMatrixBlocks + 3, kGradBlocks = kLastBlock + 3;
+
+struct GradSums {  // [slices][members] sums of a slice, strides in floats
+  float* p;
+  int slices;  // kSlices, or 1: a block adds the slices itself
+  size_t slice_stride, member_stride;
 };
 
-struct GradJobs {
-  GradJob job[4];
+// One operand of the products: this lane's element of the sample rows behind
+// `rows` (row_floats each), `at` bytes into the first of them (kNone: zero),
+// plus a constant.  Rows are taken as buffers, so that a load costs no address
+// arithmetic and 32 groups of samples are in flight (with 64-bit addresses the
+// compiler kept three: 38 us).
+struct Operand {
+  const float* rows;
+  int row_floats;
+  unsigned at;
+  float plus;
 };
 
-// One 16 x 16 tile of G per block on FP32 MFMA (v_mfma_f32_16x16x4f32,
-// A[i][k]: lane i + 16 k, B[k][j]: lane j + 16 k, D[i][j]: lane j + 16 (i/4),
-// item i % 4): A = delta (outputs x samples), B = inputs (samples x inputs,
-// the column after the last input is 1 for the bias).  The block's 4 waves
-// take interleaved groups of 4 samples, sum them in fixed order through LDS:
-// deterministic.
-__global__ __launch_bounds__(256) void wgrad_kernel(GradJobs jobs, int64_t n, float* grad) {
-  __shared__ float part[4][16][16];
-  int jn = 0;
+constexpr unsigned kNone = 0xfffffff0u;  // an offset outside every buffer
+constexpr int kU = 32;                   // groups of four samples in flight
+
+template <class V>
+__device__ inline void load_rows(const Operand& o, int64_t s, int u, bool there, V& v) {
+  const uint64_t a = (uint64_t)(o.rows + s * o.row_floats);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  const unsigned bytes = 16u * kU * o.row_floats * 4u;
+  const __amdgpu_buffer_rsrc_t r =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, bytes, 0x00027000);
+  const unsigned at = there ? o.at : kNone;
+  if constexpr (sizeof(V) == 8) v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, at, u * 64 * o.row_floats, 0));
+  else v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, at, u * 64 * o.row_floats, 0));
+}
+
+// One slice of the samples: acc[a] += A x B, the A operand one or two tiles.
+template <int NA>
+__device__ inline void slice_sum(const Operand& A, const Operand& B, int64_t n, int z, float4_t (&acc)[NA]) {
+  typedef float a_t __attribute__((ext_vector_type(NA)));
+  const int k = (threadIdx.x % 64) >> 4;
 #pragma unroll
-  for (int q = 1; q < 4; ++q)
-    if ((int)blockIdx.x >= jobs.job[q].first) jn = q;
-  const GradJob& job = jobs.job[jn];
-  const int m = blockIdx.y;
-  const float* __restrict__ delta = job.delta + m * job.delta_stride;
-  const float* __restrict__ in = job.in + m * job.in_stride;
-  const int tile = blockIdx.x - job.first;
-  const int o0 = (tile / job.tiles_x) * 16, i0 = (tile % job.tiles_x) * 16;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int r = lane & 15, k = lane >> 4;
-  const int o = o0 + r, i = i0 + r;  // A row (output) and B column (input) of this lane
-  const bool o_ok = o < job.nO;
-  const float bias_one = i == job.K ? 1.0f : 0.0f;
-  float4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  // samples sb + k with the wave-uniform base sb = 16 g + 4 wave, g = 0, 1,
-  // ...: each MFMA takes 4 samples; loop bounds are uniform over the wave
-  constexpr int kU = 32;  // MFMAs per unrolled group (loads issued ahead)
-  int64_t sb = 4 * wave;
-  for (; sb + 16 * (kU - 1) + 3 < n; sb += 16 * kU) {
-    float a[kU], b[kU];
+  for (int a = 0; a < NA; ++a) acc[a] = {0.0f, 0.0f, 0.0f, 0.0f};
+  int64_t s = 4 * z;
+  for (; s + 16 * (kU - 1) + 3 < n; s += 16 * kU) {
+    a_t x[kU];
+    float y[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int64_t su = sb + 16 * u + k;
-      a[u] = o_ok ? delta[su * job.rows_d + o] : 0.0f;
-      b[u] = i < job.K ? in[su * job.K + i] : bias_one;
+      load_rows(A, s, u, true, x[u]);
+      load_rows(B, s, u, true, y[u]);
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < kU; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u], acc, 0, 0, 0);
-  }
-  for (; sb < n; sb += 16) {  // the tail: one group of 4 samples per MFMA, missing samples as zeros
-    const int64_t su = sb + k;
-    const bool in_range = su < n;
-    const float a = in_range && o_ok ? delta[su * job.rows_d + o] : 0.0f;
-    const float b = in_range ? (i < job.K ? in[su * job.K + i] : bias_one) : 0.0f;
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-  }
+    for (int u = 0; u < kU; ++u)
 #pragma unroll
-  for (int v = 0; v < 4; ++v) part[wave][4 * k + v][r] = acc[v];  // D[4k + v][r]
-  __syncthreads();
-  {
-    const int oo = threadIdx.x / 16, ii = threadIdx.x % 16;
-    const float g = ((part[0][oo][ii] + part[1][oo][ii]) + part[2][oo][ii]) + part[3][oo][ii];
-    const int og = o0 + oo, ig = i0 + ii;
-    if (og < job.nO && ig <= job.K) {
-      float* gm = grad + (size_t)m * kP;
-      if (ig < job.K) gm[job.w_off + og * job.K + ig] = g;
-      else gm[job.b_off + og] = g;
-    }
+      for (int a = 0; a < NA; ++a)
+        acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][a], y[u] + B.plus, acc[a], 0, 0, 0);
+  }
+  for (; s < n; s += 16) {  // the rest, missing samples as zeros
+    const bool there = s + k < n;
+    a_t x;
+    float y;
+    load_rows(A, s, 0, there, x);
+    load_rows(B, s, 0, there, y);
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+      acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[a], y + (there ? B.plus : 0.0f), acc[a], 0, 0, 0);
   }
 }
-__global__ void adam_kernel(Model md, const float* grad, int M, float lr, int step) {
+
+// The slices of the block, added in order.
+template <int NA>
+__device__ inline void add_slices(const Operand& A, const Operand& B, int64_t n, int z, int slices, float4_t (&sum)[NA]) {
+  slice_sum(A, B, n, z, sum);
+  for (int q = 1; q < kSlices / slices; ++q) {
+    float4_t acc[NA];
+    slice_sum(A, B, n, z + q, acc);
+#pragma unroll
+    for (int a = 0; a < NA; ++a) sum[a] += acc[a];
+  }
+}
+
+// All blocks of a member and slice run on one XCD (the dispatcher deals blocks
+// to the 8 XCDs in turn), so that each L2 reads its own part of the activations
+// once, not every L2 all of them.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void wgrad_kernel(TrainWs ws, int64_t n,
+                                                                                             int members,
+                                                                                             GradSums sums) {
+  const int pair = blockIdx.x % 8 + 8 * (blockIdx.x / (8 * kGradBlocks));
+  if (pair >= members * sums.slices) return;
+  const int m = pair / sums.slices, z = pair % sums.slices;
+  float* out = sums.p + z * sums.slice_stride + m * sums.member_stride;
+  const size_t nh = (size_t)n * kH;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int r = lane & 15, k = lane >> 4;
+  const int x = blockIdx.x / 8 % kGradBlocks;
+  // element e of row k (the sample of the group that this lane loads)
+  auto in_row = [&](int row_floats, int e) { return (unsigned)(k * row_floats + e) * 4u; };
+  if (x < kMatrixBlocks) {
+    const int layer = x / 8, part = x % 8;  // 0: W2, 1: W3
+    const int o0 = 64 * (part & 1) + 32 * (wave & 1), i0 = 32 * (part >> 1) + 16 * (wave >> 1);
+    const Operand A{(layer ? ws.d3 : ws.d2) + m * nh, kH, in_row(kH, o0 + 2 * r), 0.0f};
+    const Operand B{(layer ? ws.h2 : ws.h1) + m * nh, kH, in_row(kH, i0 + r), 0.0f};
+    float4_t acc[2];
+    add_slices(A, B, n, z, sums.slices, acc);
+    float* w = out + (layer ? oW3 : oW2);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) w[(o0 + 2 * (4 * k + v) + a) * kH + i0 + r] = acc[a][v];  // D[4 k + v][r]
+    return;
+  }
+  if (x >= kLastBlock) {  // w4 and b4: row 0 of A is dy; B 16 units of h3, or ones
+    const int tile = 4 * (x - kLastBlock) + wave;
+    if (tile > kH / 16) return;
+    const bool ones = tile == kH / 16;
+    const Operand A{ws.dy + (size_t)m * n, 1, r == 0 ? in_row(1, 0) : kNone, 0.0f};
+    const Operand B{ws.h3 + m * nh, kH, ones ? kNone : in_row(kH, 16 * tile + r), ones ? 1.0f : 0.0f};
+    float4_t acc[1];
+    add_slices(A, B, n, z, sums.slices, acc);
+    if (k == 0) {  // D[0][r]
+      if (!ones) out[ow4 + 16 * tile + r] = acc[0][0];
+      else if (r == 0) out[ob4] = acc[0][0];
+    }
+    return;
+  }
+  // columns of B: the inputs (first layer only), then ones
+  const int layer = x - kMatrixBlocks, nin = layer == 0 ? kIn : 0;
+  const Operand A{(layer == 0 ? ws.d1 : layer == 1 ? ws.d2 : ws.d3) + m * nh, kH, in_row(kH, 32 * wave + 2 * r), 0.0f};
+  const Operand B{ws.z + (size_t)m * n * kIn, kIn, r < nin ? in_row(kIn, r) : kNone, r == nin ? 1.0f : 0.0f};
+  float4_t acc[2];
+  add_slices(A, B, n, z, sums.slices, acc);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int o = 32 * wave + 2 * (4 * k + v) + a;
+      if (r < nin) out[oW1 + o * kIn + r] = acc[a][v];
+      if (r == nin) out[(layer == 0 ? ob1 : layer == 1 ? ob2 : ob3) + o] = acc[a][v];
+    }
+}
+
+__device__ inline float summed_grad(const GradSums& sums, int m, int k) {
+  const float* p = sums.p + m * sums.member_stride + k;
+  float g = p[0];
+  for (int z = 1; z < sums.slices; ++z) g += p[z * sums.slice_stride];
+  return g;
+}
+
+__global__ void sum_grad_kernel(GradSums sums, int M, float* grad) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q < (int64_t)M * kP) grad[q] = summed_grad(sums, (int)(q / kP), (int)(q % kP));
+}
+
+__global__ void adam_kernel(Model md, GradSums sums, int M, float lr, int step) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= (int64_t)M * kP) return;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float g = grad[q];
+  const float g = summed_grad(sums, (int)(q / kP), (int)(q % kP));
   const float m = b1 * md.m[q] + (1.0f - b1) * g;
   const float v = b2 * md.v[q] + (1.0f - b2) * g * g;
   md.m[q] = m;
@@ -865,16 +822,17 @@ __global__ __launch_bounds__(1024) void loss_kernel(Model md, const float* t, in
 // out-of-box test of the standardised inputs, fallback flag and the number
 // of flagged queries per block.  Per tile of 64 queries, after the members'
 // forward passes (LDS ys, summed into ysum/ymin/ymax).
+template <int S>
 __device__ inline void query_finish(const Header& H, const float* __restrict__ X, int64_t n, int64_t s0,
                                     float spread_tol, const float* zs, float* ysum, float* ymin, float* ymax,
-                                    double (*bp)[kTileS], float* mean, float* spread, unsigned char* fallback,
+                                    double (*bp)[S], float* mean, float* spread, unsigned char* fallback,
                                     int* cnt, int* block_count) {
   const int tid = threadIdx.x;
-  base_parts(H, X, n, s0, bp);
+  base_parts<S>(H, X, n, s0, bp);
   __syncthreads();
-  if (tid < kTileS && s0 + tid < n) {
+  if (tid < S && s0 + tid < n) {
     const int64_t gs = s0 + tid;
-    const float base = (float)base_of(H, X, gs, bp, tid);
+    const float base = (float)base_of<S>(H, X, gs, bp, tid);
     ysum[tid] += (float)H.members * base;
     ymin[tid] += base;
     ymax[tid] += base;
@@ -891,13 +849,14 @@ __device__ inline void query_finish(const Header& H, const float* __restrict__ X
     if (fb) atomicAdd(cnt, 1);
   }
   __syncthreads();
-  if (tid == 0) block_count[blockIdx.x] = *cnt;
+  if (tid == 0 && block_count) block_count[blockIdx.x] = *cnt;
 }
 
+template <int S>
 __device__ inline void query_accumulate(const Header& H, int m, const float* ys, float* ysum, float* ymin,
                                         float* ymax) {
   const int tid = threadIdx.x;
-  if (tid < kTileS) {
+  if (tid < S) {
     const float v = ys[tid] * H.t_sigma + H.t_mu;
     ysum[tid] = m == 0 ? v : ysum[tid] + v;
     ymin[tid] = m == 0 ? v : fminf(ymin[tid], v);
@@ -906,30 +865,61 @@ __device__ inline void query_accumulate(const Header& H, int m, const float* ys,
   __syncthreads();
 }
 
-// Two blocks per CU (78 KB of LDS each, at most 256 registers per lane).
+// Tiles of S queries; the members in turn, each one's weights on their way
+// while the one before is computed.  64 queries per tile where that fills the
+// chip (two blocks per CU); 16 for few queries, which are then spread over
+// four times the CUs and whose chain of layers is four times shorter.
+template <int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void query_f32_kernel(
     Model md, const float* __restrict__ X, int64_t n, float spread_tol, float* mean, float* spread,
     unsigned char* fallback, int* block_count) {
-  __shared__ float zs[kTileS * kIn];
-  __shared__ float act[kTileS][kActStride];
-  __shared__ float wl[kH / 2][kWS];
-  __shared__ SmallP sp;
-  __shared__ float yp[4][kTileS];
-  __shared__ float ys[kTileS], ymin[kTileS], ymax[kTileS], ysum[kTileS];
-  __shared__ double bp[4][kTileS];
+  constexpr int NS = S / 16;
+  __shared__ float zs[S * kIn];
+  __shared__ __align__(16) float act[S][kActStride];
+  __shared__ float w4[kH + 1];
+  __shared__ float yp[4][S];
+  __shared__ float ys[S], ymin[S], ymax[S], ysum[S];
+  __shared__ double bp[kBaseParts<S>][S];
   __shared__ int cnt;
   const Header& H = *md.hdr;
-  const int64_t s0 = (int64_t)blockIdx.x * kTileS;
-  if (threadIdx.x == 0) cnt = 0;
-  WHalf pf;
-  wload_half(pf, md.master + oW2, 0);
-  for (int m = 0; m < H.members; ++m) {
+  if (H.precision != IT_MLP_FP32) return;
+  const int64_t s0 = (int64_t)blockIdx.x * S;
+  const int tid = threadIdx.x, o = unit0();
+  const int members = H.members;
+  if (tid == 0) cnt = 0;
+  WFrag fa, fb;
+  SmallP sp;
+  wload_fwd(fa, md.master + oW2);
+  sload(md.master, sp);
+  inputs_f32<S>(H, X, n, s0, zs);
+  __syncthreads();
+  for (int m = 0; m < members; ++m) {
     const float* master = md.master + (size_t)m * kP;
-    const float* next = m + 1 < H.members ? master + kP + oW2 : nullptr;
-    forward_query_f32(H, master, X, n, s0, zs, act, wl, sp, yp, ys, pf, next);
-    query_accumulate(H, m, ys, ysum, ymin, ymax);
+    if (tid < kH + 1) w4[tid] = master[ow4 + tid];  // its last readers passed a barrier
+    auto put = [&](int s, float x, float y) { *(float2_t*)&act[s][o] = float2_t{x, y}; };
+    each_sample<S>(
+        [&](int, int, int s) { put(s, silu(first_layer(sp, zs, s, 0)), silu(first_layer(sp, zs, s, 1))); });
+    __syncthreads();
+    float4_t acc[NS][2];
+    wload_fwd(fb, master + oW3);
+    mm_f32<S>(act, fa, acc);
+    __syncthreads();  // every wave has read the activations
+    each_sample<S>(
+        [&](int st, int v, int s) { put(s, silu(acc[st][0][v] + sp.b2[0]), silu(acc[st][1][v] + sp.b2[1])); });
+    __syncthreads();
+    if (m + 1 < members) wload_fwd(fa, master + kP + oW2);
+    mm_f32<S>(act, fb, acc);
+    __syncthreads();
+    each_sample<S>(
+        [&](int st, int v, int s) { put(s, silu(acc[st][0][v] + sp.b3[0]), silu(acc[st][1][v] + sp.b3[1])); });
+    if (m + 1 < members) sload(master + kP, sp);
+    __syncthreads();
+    dots_f32<S>(act, w4, yp);
+    __syncthreads();
+    if (tid < S) ys[tid] = output_f32<S>(w4, yp, tid);
+    query_accumulate<S>(H, m, ys, ysum, ymin, ymax);
   }
-  query_finish(H, X, n, s0, spread_tol, zs, ysum, ymin, ymax, bp, mean, spread, fallback, &cnt, block_count);
+  query_finish<S>(H, X, n, s0, spread_tol, zs, ysum, ymin, ymax, bp, mean, spread, fallback, &cnt, block_count);
 }
 
 __global__ __launch_bounds__(256) void query_bf16_kernel(Model md, const float* __restrict__ X, int64_t n,
@@ -938,18 +928,20 @@ __global__ __launch_bounds__(256) void query_bf16_kernel(Model md, const float* 
   __shared__ float zs[kTileS * kIn];
   __shared__ unsigned short act[2][kTileS][kActStride];
   __shared__ float ys[kTileS], ymin[kTileS], ymax[kTileS], ysum[kTileS];
-  __shared__ double bp[4][kTileS];
+  __shared__ double bp[kBaseParts<kTileS>][kTileS];
   __shared__ int cnt;
   const Header& H = *md.hdr;
+  if (H.precision != IT_MLP_BF16) return;
+  const unsigned short* weights = bf16_weights(md, H.members);
   const int64_t s0 = (int64_t)blockIdx.x * kTileS;
   if (threadIdx.x == 0) cnt = 0;
   const ForwardOut none{};
   for (int m = 0; m < H.members; ++m) {
-    forward_tile_bf16<false>(H, md.master + (size_t)m * kP, md.w + (size_t)m * kPpad, X, n, s0, zs, act, ys,
+    forward_tile_bf16<false>(H, md.master + (size_t)m * kP, weights + (size_t)m * kPpad, X, n, s0, zs, act, ys,
                              none);
-    query_accumulate(H, m, ys, ysum, ymin, ymax);
+    query_accumulate<kTileS>(H, m, ys, ysum, ymin, ymax);
   }
-  query_finish(H, X, n, s0, spread_tol, zs, ysum, ymin, ymax, bp, mean, spread, fallback, &cnt, block_count);
+  query_finish<kTileS>(H, X, n, s0, spread_tol, zs, ysum, ymin, ymax, bp, mean, spread, fallback, &cnt, block_count);
 }
 // Ordered compaction of the flagged query indices: an exclusive scan of the
 // per-block counts (one block), then each block writes its flagged indices
@@ -977,16 +969,56 @@ __global__ __launch_bounds__(1024) void scan_kernel(const int* block_count, int 
   if (threadIdx.x == 0) *total = carry;
 }
 
+// As many flagged queries as lie before tile b, the sum of the tiles' counts
+// in front of it: with few tiles cheaper than a scan in a launch of its own.
+constexpr int kScanTiles = 4096;  // tiles from which the scan is one
+
+// off: the scan's offsets, or null: summed here (and the total written by the
+// last block).
 __global__ __launch_bounds__(kTileS) void scatter_kernel(const unsigned char* fallback, int64_t n,
-                                                         const int* block_off, int64_t* idx) {
+                                                         const int* block_count, const int* off, int64_t* total,
+                                                         int64_t* idx) {
   const int64_t s0 = (int64_t)blockIdx.x * kTileS;
   const int64_t gs = s0 + threadIdx.x;
   const bool f = gs < n && fallback[gs];
   const unsigned long long mask = __ballot(f);
-  if (f) {
-    const unsigned long long below = mask & ((1ull << threadIdx.x) - 1ull);
-    idx[block_off[blockIdx.x] + __popcll(below)] = gs;
+  int first;
+  if (off) {
+    first = off[blockIdx.x];
+  } else {
+    int v = 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kTileS) v += block_count[b];
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+    first = v;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = first + __popcll(mask);
   }
+  if (f && idx) {
+    const unsigned long long below = mask & ((1ull << threadIdx.x) - 1ull);
+    idx[first + __popcll(below)] = gs;
+  }
+}
+
+// The same for few queries, from their flags, by one block.
+__global__ __launch_bounds__(1024) void compact_kernel(const unsigned char* fallback, int64_t n, int64_t* total,
+                                                       int64_t* idx) {
+  __shared__ int count[16];
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  int first = 0;
+  for (int64_t s0 = 0; s0 < n; s0 += 1024) {
+    const int64_t gs = s0 + threadIdx.x;
+    const bool f = gs < n && fallback[gs];
+    const unsigned long long mask = __ballot(f);
+    if (lane == 0) count[wave] = __popcll(mask);
+    __syncthreads();
+    int before = first;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) before += count[w];
+      first += count[w];
+    }
+    if (f && idx) idx[before + __popcll(mask & ((1ull << lane) - 1ull))] = gs;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *total = first;
 }
 
 __global__ void baseline_kernel(Model md, const float* X, int64_t n, double* out) {
@@ -1079,29 +1111,26 @@ int it_mlp_train_ws_bytes(int32_t members, int64_t n, size_t* bytes) {
   return IT_OK;
 }
 
+// The slices' sums go where the pre-activations stood, which nothing reads any
+// more then; with few samples that is too small, and few blocks do: each then
+// adds the slices itself, into the gradient's place.
+static GradSums grad_sums(const TrainWs& w, int M, int64_t n) {
+  if ((size_t)n * 3 * kH >= (size_t)kSlices * kPpad) return GradSums{w.a1, kSlices, (size_t)M * kPpad, (size_t)kPpad};
+  return GradSums{w.grad, 1, 0, (size_t)kP};
+}
+
 static int launch_grad(const Model& md, int M, bool f32, const float* X, const float* t, int64_t n,
-                       const TrainWs& w, hipStream_t s) {
-  const int nb = (int)((n + kTileS - 1) / kTileS);
+                       const TrainWs& w, const GradSums& sums, hipStream_t s) {
   if (f32) {
+    const int nb = (int)((n + kTrainS - 1) / kTrainS);
     hipLaunchKernelGGL(train_tile_f32_kernel, dim3(nb, M), dim3(256), 0, s, md, X, t, n, w);
   } else {
+    const int nb = (int)((n + kTileS - 1) / kTileS);
     hipLaunchKernelGGL(forward_train_bf16_kernel, dim3(nb, M), dim3(256), 0, s, md, X, n, w);
     hipLaunchKernelGGL(delta_bf16_kernel, dim3((unsigned)n, M), dim3(kH), 0, s, md, t, n, w);
   }
-  const size_t nh = (size_t)n * kH;
-  GradJobs jobs = {{
-      {w.d3, kH, w.h2, kH, kH, oW3, ob3, nh, nh, 0, 0},
-      {w.d2, kH, w.h1, kH, kH, oW2, ob2, nh, nh, 0, 0},
-      {w.d1, kH, w.z, kIn, kH, oW1, ob1, nh, (size_t)n * kIn, 0, 0},
-      {w.dy, 1, w.h3, kH, 1, ow4, ob4, (size_t)n, nh, 0, 0},
-  }};
-  int blocks = 0;
-  for (GradJob& g : jobs.job) {
-    g.tiles_x = (g.K + 1 + 15) / 16;
-    g.first = blocks;
-    blocks += g.tiles_x * ((g.nO + 15) / 16);
-  }
-  hipLaunchKernelGGL(wgrad_kernel, dim3(blocks, M), dim3(256), 0, s, jobs, n, w.grad);
+  hipLaunchKernelGGL(wgrad_kernel, dim3((M * sums.slices + 7) / 8 * 8 * kGradBlocks), dim3(256), 0, s, w, n,
+                     M, sums);
   return hipGetLastError() == hipSuccess ? IT_OK : IT_EHIP;
 }
 
@@ -1117,10 +1146,10 @@ int it_mlp_grad(const void* d_model, int32_t members, const float* d_X, const fl
   if (hipMemcpyAsync(&h, md.hdr, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return IT_EHIP;
-  int rc = launch_grad(md, members, h.precision == IT_MLP_FP32, d_X, d_t, n, w, s);
+  const GradSums sums = grad_sums(w, members, n);
+  int rc = launch_grad(md, members, h.precision == IT_MLP_FP32, d_X, d_t, n, w, sums, s);
   if (rc) return rc;
-  if (hipMemcpyAsync(d_grad, w.grad, (size_t)members * kP * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
-    return IT_EHIP;
+  hipLaunchKernelGGL(sum_grad_kernel, dim3((members * kP + 255) / 256), dim3(256), 0, s, sums, members, d_grad);
   if (h_loss) {
     hipLaunchKernelGGL(loss_kernel, dim3(members), dim3(1024), 0, s, md, d_t, n, w);
     if (hipMemcpyAsync(h_loss, w.loss, members * 4, hipMemcpyDeviceToHost, s) != hipSuccess) return IT_EHIP;
@@ -1146,13 +1175,14 @@ int it_mlp_train(void* d_model, int32_t members, const float* d_X, const float* 
       hipStreamSynchronize(s) != hipSuccess)
     return IT_EHIP;
   const int64_t nbatch = n / rows;
+  const GradSums sums = grad_sums(w, members, rows);
   int nlog = 0;
   for (int k = 0; k < steps; ++k) {
     // minibatch: the next contiguous window of the data, continuing across calls
     const int64_t b0 = ((h.step + k) % nbatch) * rows;
     const float* X = d_X + b0 * kIn;
     const float* t = d_t + b0;
-    int rc = launch_grad(md, members, h.precision == IT_MLP_FP32, X, t, rows, w, s);
+    int rc = launch_grad(md, members, h.precision == IT_MLP_FP32, X, t, rows, w, sums, s);
     if (rc) return rc;
     if (h_loss && log_every > 0 && k % log_every == 0) {
       hipLaunchKernelGGL(loss_kernel, dim3(members), dim3(1024), 0, s, md, t, rows, w);
@@ -1165,7 +1195,7 @@ int it_mlp_train(void* d_model, int32_t members, const float* d_X, const float* 
     const double frac = steps > 1 ? (double)k / (double)(steps - 1) : 0.0;
     const double lr0 = lr, lr1 = lr_final;  // in FP64: the end points are exact
     const float lr_k = (float)(lr1 + 0.5 * (lr0 - lr1) * (1.0 + std::cos(M_PI * frac)));
-    hipLaunchKernelGGL(adam_kernel, dim3((members * kP + 255) / 256), dim3(256), 0, s, md, w.grad, members, lr_k,
+    hipLaunchKernelGGL(adam_kernel, dim3((members * kP + 255) / 256), dim3(256), 0, s, md, sums, members, lr_k,
                        h.step + k + 1);
     if (hipGetLastError() != hipSuccess) return IT_EHIP;
   }
@@ -1204,26 +1234,34 @@ int query(const void* d_model, const float* d_X, int64_t nq, float spread_tol, f
     if (h_nfallback) *h_nfallback = 0;
     return IT_OK;
   }
-  Model md = carve_model((void*)d_model, 1);  // header and first arrays; members read from the header
-  Header h;
-  if (hipMemcpyAsync(&h, md.hdr, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return IT_EHIP;
-  md = carve_model((void*)d_model, h.members);
+  const Model md = carve_model((void*)d_model, 1);  // header and master weights; the kernels read the members
   const int nb = (int)((nq + kTileS - 1) / kTileS);
   char* p = (char*)d_ws;
   int* counts = (int*)p;
   int* offs = (int*)(p + align256((size_t)nb * 4));
   int64_t* total = (int64_t*)(p + 2 * align256((size_t)nb * 4));
-  if (h.precision == IT_MLP_FP32)
-    hipLaunchKernelGGL(query_f32_kernel, dim3(nb), dim3(256), 0, s, md, d_X, nq, spread_tol, d_mean, d_spread,
-                       d_fallback, counts);
+  // The model's precision stands in its header: both kernels are launched, and
+  // the other one's blocks end at once (reading the header back first took a
+  // copy and a synchronisation, 20 us).  Few queries go in tiles of 16 and are
+  // compacted by one block: 8192 of them are still two blocks per CU.
+  const bool few = nq <= kFewQueries;
+  if (few)
+    hipLaunchKernelGGL(query_f32_kernel<16>, dim3((unsigned)((nq + 15) / 16)), dim3(256), 0, s, md, d_X, nq, spread_tol,
+                       d_mean, d_spread, d_fallback, (int*)nullptr);
   else
-    hipLaunchKernelGGL(query_bf16_kernel, dim3(nb), dim3(256), 0, s, md, d_X, nq, spread_tol, d_mean, d_spread,
+    hipLaunchKernelGGL(query_f32_kernel<kTileS>, dim3(nb), dim3(256), 0, s, md, d_X, nq, spread_tol, d_mean, d_spread,
                        d_fallback, counts);
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, counts, nb, offs, total);
-  if (d_fallback_idx)
-    hipLaunchKernelGGL(scatter_kernel, dim3(nb), dim3(kTileS), 0, s, d_fallback, nq, offs, d_fallback_idx);
+  hipLaunchKernelGGL(query_bf16_kernel, dim3(nb), dim3(256), 0, s, md, d_X, nq, spread_tol, d_mean, d_spread,
+                     d_fallback, counts);
+  if (few) {
+    hipLaunchKernelGGL(compact_kernel, dim3(1), dim3(1024), 0, s, d_fallback, nq, total, d_fallback_idx);
+  } else {
+    const bool scan = nb > kScanTiles;
+    if (scan) hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, counts, nb, offs, total);
+    if (!scan || d_fallback_idx)
+      hipLaunchKernelGGL(scatter_kernel, dim3(nb), dim3(kTileS), 0, s, d_fallback, nq, counts, scan ? offs : nullptr,
+                         total, d_fallback_idx);
+  }
   if (hipGetLastError() != hipSuccess) return IT_EHIP;
   if (h_nfallback) {
     if (hipMemcpyAsync(h_nfallback, total, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
