@@ -209,8 +209,8 @@ typedef struct {
 
 /* Kernel selection for the stepping.  NULL means "defaults". */
 #define IT_KERNEL_AUTO 0     /* the library's choice: passes of 3 fused steps (the blocked kernel)
-                              * on grids of at least 4e6 interior nodes, 64 x 32 nodes
-                              * per plane or more, when no final fields are asked for and no
+                              * on grids of at least 1.2e6 interior nodes that its tiles
+                              * mostly cover, when no final fields are asked for (or stop_tol is 0) and no
                               * one-step tile option is set; else one step per launch.  A
                               * steps_per_pass > 0 is taken as given. */
 #define IT_KERNEL_PLAIN 1    /* one time step per launch */

@@ -32,34 +32,34 @@ __device__ inline int find_instance(const BatchInstance* inst, int ninst, int L)
 // parity, so the tile blocks of a pass read a flag the previous pass wrote.
 __device__ inline void record_previous(const BatchInstance& bi, int parity, int T) {
   const StepParams& p = bi.sp[parity ^ 1];
-  if (p.state->done) return;
+  __shared__ RunState now;
+  snapshot_state(p.state, &now);
+  __syncthreads();
+  if (now.done) return;
   // the previous pass's tile count, which its own recording block stored
   // (the host may have re-tiled the running instances since)
-  __shared__ int nprev;
-  if (threadIdx.x == 0 && threadIdx.y == 0) nprev = p.state->rec_ntiles;
-  __syncthreads();
   __shared__ double totals[kAcc * kMaxT];
-  reduce_partials(p.partials, nprev, kAcc * T, kAcc * T, totals);
+  reduce_partials(p.partials, now.rec_ntiles, kAcc * T, kAcc * T, totals);
   if (threadIdx.x == 0 && threadIdx.y == 0) {
     RunState* st = p.state;
-    const int64_t step = st->steps;
+    const int64_t step = now.steps;
     const int Te = (int)min((int64_t)T, bi.max_steps - step);
     const bool train = bi.npulses >= 2;
     int inject = -1;
     if (train) {
       if (step == 0) {
-        st->pulse_q[0] = st->released;
-        st->pulse_q[1] = st->released_neg;
+        now.pulse_q[0] = st->pulse_q[0] = now.released;
+        now.pulse_q[1] = st->pulse_q[1] = now.released_neg;
       }
-      const int k = st->pulses_counted;
+      const int k = now.pulses_counted;
       const int64_t s_k = (int64_t)k * bi.period_steps;
       if (k < bi.npulses && s_k >= step && s_k < step + Te) {
         inject = (int)(s_k - step);
         st->pulses_counted = k + 1;
       }
     }
-    finalize_steps(st, p.trace, totals, Te, step, p.cp, p.cn, p.dV, p.stop_tol, p.min_stop_step, inject,
-                   train ? st->pulse_q[0] : 0.0, train ? st->pulse_q[1] : 0.0);
+    finalize_steps(st, &now, p.trace, totals, Te, step, p.cp, p.cn, p.dV, p.stop_tol, p.min_stop_step, inject,
+                   train ? now.pulse_q[0] : 0.0, train ? now.pulse_q[1] : 0.0);
     if (!st->done && st->steps >= bi.max_steps) {
       st->done = 1;
       st->by_limit = 1;
@@ -69,7 +69,7 @@ __device__ inline void record_previous(const BatchInstance& bi, int parity, int 
       // the next pass computes steps c1 .. c1 + T - 1; a pulse at or past
       // the run's last step is never deposited
       const int64_t c1 = step + 2 * T;
-      const int kf = st->pulses_flagged;
+      const int kf = now.pulses_flagged;
       const int64_t s_due = (int64_t)kf * bi.period_steps;
       const bool due = kf < bi.npulses && s_due > c1 && s_due <= c1 + T && s_due < bi.max_steps;
       st->pulse_add[parity ^ 1] = due ? (int)(s_due - c1) : 0;

@@ -179,10 +179,12 @@ struct Step3Params {
   int tiles_x, tiles_y, zchunks, zc, ntiles, per_xcd;
   Coef co[3];
   double beta, dV, stop_tol;
-  double* partials;         // [gridDim][kAcc3]
+  double* partials;         // [tiles' blocks][kAcc3]
+  const double* prev_partials;  // when set, an extra block records the previous step from them
   RunState* state;
 };
 hipError_t launch_step3(const Step3Params& p, hipStream_t s);
+hipError_t launch_reduce3(const Step3Params& p, hipStream_t s);  // records the step of p.partials
 
 // Launch errors are read with hipGetLastError(), which also returns an error
 // left by any earlier HIP call of the thread (the caller's included).  Entry

@@ -35,7 +35,7 @@ void batch_step_kernel(const BatchInstance* __restrict__ inst, int ninst, int to
   if (L >= total_tiles) return;
   const int q = find_instance(inst, ninst, L);
   const StepParams& p = inst[q].sp[parity];
-  if (p.state->done) return;
+  const int done = p.state->done;
   const int l = L - inst[q].tile_begin;
   TileCoord t = tile_of(l, p.tiles_x, p.tiles_y);
   t.valid = true;
@@ -43,10 +43,10 @@ void batch_step_kernel(const BatchInstance* __restrict__ inst, int ninst, int to
     const BatchInstance& bi = inst[q];
     // written by the previous pass's recording block; one value for the block
     const int add = bi.npulses >= 2 ? __builtin_amdgcn_readfirstlane(p.state->pulse_add[parity]) : 0;
-    plain_tile_step<SY, SC, AB, TX, true>(p, t, p.partials + (size_t)l * kAcc, add ? bi.pulse_pos : nullptr,
+    plain_tile_step<SY, SC, AB, TX, true>(p, t, done, p.partials + (size_t)l * kAcc, add ? bi.pulse_pos : nullptr,
                                           add ? bi.pulse_neg : nullptr);
   } else {
-    plain_tile_step<SY, SC, AB, TX>(p, t, p.partials + (size_t)l * kAcc);
+    plain_tile_step<SY, SC, AB, TX>(p, t, done, p.partials + (size_t)l * kAcc);
   }
 }
 

@@ -18,11 +18,12 @@ constexpr int kMinT = 2, kMaxBlockedT = 4;  // T = 5 would need 170 KB of LDS fo
 // Records the previous pass (its partials, block count and step count come
 // with the launch): the extra block of a launch.
 __device__ void record_previous_pass(const StepParams& p) {
-  if (p.state->done) return;
+  __shared__ RunState now;
   __shared__ double totals[kAcc * kMaxT];
+  snapshot_state(p.state, &now);
   reduce_partials<kBNT>(p.prev_partials, p.prev_nblocks, kAcc * p.prev_T, kAcc * p.prev_T, totals);
-  if (threadIdx.x == 0 && threadIdx.y == 0)
-    finalize_steps(p.state, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
+  if (!now.done && threadIdx.x == 0 && threadIdx.y == 0)
+    finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
                    p.min_stop_step);
 }
 

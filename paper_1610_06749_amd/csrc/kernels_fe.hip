@@ -17,6 +17,41 @@ namespace {
 
 constexpr int kTX3 = 64, kTY3 = 8, kNT3 = kTX3 * kTY3;
 
+// One block: the step's totals in fixed order, then the run state.  The
+// electron phase records no per-step trace; its ion tallies join the run's
+// totals, and the deposit's released counts are consumed here (the ion phase
+// that follows records no release).
+__device__ inline void record_step3(const Step3Params& p, const double* partials, int nblocks) {
+  __shared__ RunState now;
+  __shared__ double tot[kAcc3];
+  snapshot_state(p.state, &now);
+  reduce_partials(partials, nblocks, kAcc3, kAcc3, tot);
+  if (now.e_done || threadIdx.x != 0 || threadIdx.y != 0) return;
+  RunState& st = now;
+  const double dV = p.dV;
+  const double col[6] = {p.co[0].azp * tot[2] * dV, p.co[0].azm * tot[3] * dV, p.co[1].azp * tot[4] * dV,
+                         p.co[1].azm * tot[5] * dV, p.co[2].azp * tot[6] * dV, p.co[2].azm * tot[7] * dV};
+  st.sums[0] += tot[0] * dV;
+  for (int q = 0; q < 4; ++q) st.sums[1 + q] += col[q];
+  st.e_sums[0] += col[4];
+  st.e_sums[1] += col[5];
+  st.e_sums[2] += tot[1] * dV;
+  st.e_left = tot[10] * dV;
+  st.released_pending = 0.0;
+  st.released_pending_neg = 0.0;
+  st.e_steps += 1;
+  bool finite = true;
+  for (int q = 0; q < kAcc3; ++q) finite = finite && isfinite(tot[q]);
+  if (!finite) {
+    st.flags |= IT_FLAG_NONFINITE;
+    st.e_done = 1;
+    st.done = 1;
+  } else if (tot[13] * dV <= p.stop_tol * st.released_e) {
+    st.e_done = 1;
+  }
+  *p.state = st;
+}
+
 struct Regs3 {
   double v[3];
 };
@@ -25,6 +60,12 @@ struct Regs3 {
 // n+, n-, n_e on plane 1 and plane nz-1 (anode, cathode per carrier),
 // 8..10 in-flight sums, 11..13 sums of |n|
 __global__ __launch_bounds__(kNT3) __attribute__((amdgpu_waves_per_eu(4, 8))) void step3_kernel(Step3Params p) {
+  // As in the one-step ion kernel: with prev_partials one block more than
+  // tiles, which records the previous step while the others compute this one.
+  if (p.prev_partials && blockIdx.x == gridDim.x - 1) {
+    record_step3(p, p.prev_partials, (int)gridDim.x - 1);
+    return;
+  }
   if (p.state->e_done) return;
   __shared__ double sl[2][3][kTY3 + 2][kTX3 + 2];
   __shared__ double lds[(kNT3 / kWave) * kAcc3];
@@ -126,52 +167,24 @@ __global__ __launch_bounds__(kNT3) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     if (k + 3 >= k1) break;
     plane_step(k + 3, 1, r3, r0, r1, r2, rb, ra);
   }
-  __syncthreads();
+  lds_barrier();
   block_sum_store<kAcc3, kNT3>(acc, p.partials + (size_t)blockIdx.x * kAcc3, lds);
 }
 
-// One block: the step's totals in fixed order, then the run state.  The
-// electron phase records no per-step trace; its ion tallies join the run's
-// totals, and the deposit's released counts are consumed here (the ion phase
-// that follows records no release).
 __global__ __launch_bounds__(1024) void reduce3_kernel(Step3Params p, int nblocks) {
-  if (p.state->e_done) return;
-  __shared__ double tot[kAcc3];
-  reduce_partials<1024>(p.partials, nblocks, kAcc3, kAcc3, tot);
-  if (threadIdx.x != 0) return;
-  RunState st = *p.state;
-  const double dV = p.dV;
-  const double col[6] = {p.co[0].azp * tot[2] * dV, p.co[0].azm * tot[3] * dV, p.co[1].azp * tot[4] * dV,
-                         p.co[1].azm * tot[5] * dV, p.co[2].azp * tot[6] * dV, p.co[2].azm * tot[7] * dV};
-  st.sums[0] += tot[0] * dV;
-  for (int q = 0; q < 4; ++q) st.sums[1 + q] += col[q];
-  st.e_sums[0] += col[4];
-  st.e_sums[1] += col[5];
-  st.e_sums[2] += tot[1] * dV;
-  st.e_left = tot[10] * dV;
-  st.released_pending = 0.0;
-  st.released_pending_neg = 0.0;
-  st.e_steps += 1;
-  bool finite = true;
-  for (int q = 0; q < kAcc3; ++q) finite = finite && isfinite(tot[q]);
-  if (!finite) {
-    st.flags |= IT_FLAG_NONFINITE;
-    st.e_done = 1;
-    st.done = 1;
-  } else if (tot[13] * dV <= p.stop_tol * st.released_e) {
-    st.e_done = 1;
-  }
-  *p.state = st;
+  record_step3(p, p.partials, nblocks);
 }
 
 }  // namespace
 
 hipError_t launch_step3(const Step3Params& p, hipStream_t s) {
   const int grid = 8 * p.per_xcd;
-  hipLaunchKernelGGL(step3_kernel, dim3(grid), dim3(kTX3, kTY3), 0, s, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce3_kernel, dim3(1), dim3(1024), 0, s, p, grid);
+  hipLaunchKernelGGL(step3_kernel, dim3(grid + (p.prev_partials ? 1 : 0)), dim3(kTX3, kTY3), 0, s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce3(const Step3Params& p, hipStream_t s) {
+  hipLaunchKernelGGL(reduce3_kernel, dim3(1), dim3(1024), 0, s, p, 8 * p.per_xcd);
   return hipGetLastError();
 }
 

@@ -31,20 +31,23 @@ namespace it {
 template <int SY, bool SC, bool AB, int TX>
 __global__ __launch_bounds__(kTX * SY) __attribute__((amdgpu_waves_per_eu(TX == 2 * kTX ? 2 : 4, 8))) void step_plain_kernel(StepParams p) {
   if (p.prev_partials && blockIdx.x == gridDim.x - 1) {
-    if (p.state->done) return;
+    __shared__ RunState now;
     __shared__ double totals[kAcc * kMaxT];
+    snapshot_state(p.state, &now);
     reduce_partials<kTX * SY>(p.prev_partials, p.prev_nblocks, kAcc * p.prev_T, kAcc * p.prev_T, totals);
-    if (threadIdx.x == 0 && threadIdx.y == 0)
-      finalize_steps(p.state, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
+    if (!now.done && threadIdx.x == 0 && threadIdx.y == 0)
+      finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
                      p.min_stop_step);
     return;
   }
-  if (p.state->done) return;  // set by an earlier launch: every block skips
+  // set by an earlier launch: every block skips (read here, looked at once the
+  // first planes are on their way)
+  const int done = p.state->done;
   const TileCoord t = decode_tile(p.tiles_x, p.tiles_y, p.ntiles, p.per_xcd);
   if constexpr (TX == 2 * kTX)
-    pair_tile_step<SY, SC, AB>(p, t, p.partials + (size_t)blockIdx.x * kAcc);
+    pair_tile_step<SY, SC, AB>(p, t, done, p.partials + (size_t)blockIdx.x * kAcc);
   else
-    plain_tile_step<SY, SC, AB, TX>(p, t, p.partials + (size_t)blockIdx.x * kAcc);
+    plain_tile_step<SY, SC, AB, TX>(p, t, done, p.partials + (size_t)blockIdx.x * kAcc);
 }
 
 // One block: sums the per-block partial tallies of a stepping launch in a
@@ -56,7 +59,7 @@ __global__ __launch_bounds__(1024) void reduce_steps_kernel(StepParams p, int nb
   __shared__ double totals[kAcc * kMaxT];
   reduce_partials<1024>(p.partials, nblocks, kAcc * T, kAcc * T, totals);
   if (threadIdx.x == 0)
-    finalize_steps(p.state, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol,
+    finalize_steps(p.state, p.state, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol,
                    p.min_stop_step);
 }
 

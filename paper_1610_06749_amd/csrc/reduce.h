@@ -67,7 +67,7 @@ __device__ inline void block_sum_store(double (&acc)[N], double* out, double* ld
     const double v = (ZERO >> q) & 1u ? 0.0 : (LANE0 >> q) & 1u ? acc[q] : wave_sum(acc[q]);
     if (lane == 0) lds[wave * N + q] = v;
   }
-  __syncthreads();
+  lds_barrier();  // not __syncthreads(), which would wait for the stores of the block's fields
   if (tid < N) {
     double s = lds[tid];
 #pragma unroll
@@ -98,11 +98,11 @@ __device__ inline bool arrive_last(unsigned* counter, unsigned nblocks) {
   return last != 0;
 }
 
-// In the last block: totals[q] = sum over blocks b of partials[b * stride + q]
-// for q < n.  Component q is reduced by wave q % W; its lanes take the blocks
-// in a fixed stride (8 independent loads in flight each) and the wave sums
-// them by a fixed butterfly, so all components finish in a few round trips.
-// NT: threads of the block (0: as launched).
+// totals[q] = sum over blocks b of partials[b * stride + q] for q < n.
+// Component q is reduced by wave q % W, two components at a time; its lanes
+// take the blocks in a fixed stride (8 independent loads in flight each) and the
+// wave sums them in a fixed order, so all components finish in a few round
+// trips.  NT: threads of the block (0: as launched).  Ends with a barrier.
 template <int NT = 0>
 __device__ inline void reduce_partials(const double* partials, int nblocks, int stride, int n,
                                        double* totals) {
@@ -110,50 +110,68 @@ __device__ inline void reduce_partials(const double* partials, int nblocks, int 
   constexpr int kBatch = 8;
   const int tid = threadIdx.x + threadIdx.y * blockDim.x;
   const int wave = tid / kWave, lane = tid % kWave;
-  for (int q = wave; q < n; q += W) {
-    double s = 0.0;
+  for (int q = wave; q < n; q += 2 * W) {
+    const int q2 = q + W < n ? q + W : q;
+    double s = 0.0, s2 = 0.0;
     for (int b0 = lane; b0 < nblocks; b0 += kWave * kBatch) {
-      double v[kBatch];
+      double v[kBatch], v2[kBatch];
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int b = b0 + u * kWave;
         v[u] = b < nblocks ? partials[(size_t)b * stride + q] : 0.0;
+        v2[u] = b < nblocks ? partials[(size_t)b * stride + q2] : 0.0;
       }
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) s += v[u];
+      for (int u = 0; u < kBatch; ++u) {
+        s += v[u];
+        s2 += v2[u];
+      }
     }
     s = wave_sum(s);
-    if (lane == 0) totals[q] = s;
+    s2 = wave_sum(s2);
+    if (lane == 0) {
+      totals[q] = s;
+      totals[q2] = s2;
+    }
   }
   __syncthreads();
+}
+
+// Copies the run state into LDS, where the recording thread reads it after
+// the next barrier: its loads then overlap those of the partial sums.
+__device__ inline void snapshot_state(const RunState* st, RunState* snap) {
+  static_assert(sizeof(RunState) % 4 == 0, "copied in words");
+  const int tid = threadIdx.x + threadIdx.y * blockDim.x, nt = blockDim.x * blockDim.y;
+  for (int i = tid; i < (int)(sizeof(RunState) / 4); i += nt) ((uint32_t*)snap)[i] = ((const uint32_t*)st)[i];
 }
 
 // Thread 0 of the last block: turns the reduced sums of T consecutive steps
 // (tot[s * kAcc + q]) into trace records and updates the run state and the
 // stop decision (trace may be NULL: no per-step records kept).  Works on
 // register copies of the fields it updates (a whole-struct copy would pass
-// the untouched fields through private memory).  inject_at >= 0: a pulse of
+// the untouched fields through private memory); now: the state as it stands
+// (gst itself, or a copy in LDS).  inject_at >= 0: a pulse of
 // a batched pulse train released inj_pos and inj_neg ions before the step
 // step0 + inject_at, which are booked with that step.
-__device__ inline void finalize_steps(RunState* gst, double* trace, const double* tot, int T,
+__device__ inline void finalize_steps(RunState* gst, const RunState* now, double* trace, const double* tot, int T,
                                       int64_t step0, const Coef& cp, const Coef& cn, double dV,
                                       double stop_tol, int64_t min_stop_step, int inject_at = -1,
                                       double inj_pos = 0.0, double inj_neg = 0.0) {
-  double released = gst->released, released_neg = gst->released_neg;
-  double pending = gst->released_pending, pending_neg = gst->released_pending_neg;
+  double released = now->released, released_neg = now->released_neg;
+  double pending = now->released_pending, pending_neg = now->released_pending_neg;
   double sums[5], last[4], screened[2], escaped[2];
 #pragma unroll
-  for (int q = 0; q < 5; ++q) sums[q] = gst->sums[q];
+  for (int q = 0; q < 5; ++q) sums[q] = now->sums[q];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    screened[q] = gst->screened[q];
-    escaped[q] = gst->escaped[q];
+    screened[q] = now->screened[q];
+    escaped[q] = now->escaped[q];
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) last[q] = gst->last[q];
-  int64_t steps = gst->steps;
-  int done = gst->done, flags = gst->flags;
-  const int64_t period_step = gst->period_step;
+  for (int q = 0; q < 4; ++q) last[q] = now->last[q];
+  int64_t steps = now->steps;
+  int done = now->done, flags = now->flags;
+  const int64_t period_step = now->period_step;
   bool injected = false;
   for (int s = 0; s < T && !done; ++s) {
     const int64_t l = step0 + s;
@@ -217,7 +235,7 @@ __device__ inline void finalize_steps(RunState* gst, double* trace, const double
   if (injected) {
     gst->released = released;
     gst->released_neg = released_neg;
-    gst->released_q += inj_neg;  // negative charge: the ions (no free electrons in a train)
+    gst->released_q = now->released_q + inj_neg;  // negative charge: the ions (no free electrons in a train)
   }
 #pragma unroll
   for (int q = 0; q < 5; ++q) gst->sums[q] = sums[q];
@@ -231,7 +249,7 @@ __device__ inline void finalize_steps(RunState* gst, double* trace, const double
   gst->steps = steps;
   gst->done = done;
   gst->flags = flags;
-  gst->passes += 1;
+  gst->passes = now->passes + 1;
 }
 
 // Tile coordinates: column tile (tx, ty) and z chunk.

@@ -26,7 +26,8 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kBlockedT = 3;                // steps per pass of the blocked kernel when none is given
-constexpr double kBlockedMinNodes = 4.0e6;  // interior nodes from which the library chooses it
+constexpr double kBlockedMinNodes = 1.2e6;  // interior nodes from which the library chooses it
+constexpr double kBlockedTallNodes = 5.0e6;  // and from which its tiles have four rows per thread, not three
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -383,24 +384,42 @@ int requested_steps(const it_exec* ex) {
 }
 
 // The library's choice: passes of kBlockedT steps of the blocked kernel on a
-// grid large enough to fill the machine (on MI355X 1.8x faster per
-// step than one step per launch at 13 M and 67 M interior nodes), else one
-// step per launch.  Not when the caller sets a one-step tile option, and not
-// when the final fields are asked for: a blocked pass that contains the step
-// meeting the collection criterion still computes the pass's later steps,
-// so its fields would be up to kBlockedT - 1 steps past the result's.
-int auto_steps(const it_chamber* ch, const it_exec* ex, bool exact_fields) {
-  if (exact_fields) return 1;
+// grid of kBlockedMinNodes interior nodes or more that its tiles cover without
+// idling for the most part, else one step per launch.  On MI355X, us per step,
+// one step per launch and blocked (three rows per thread): 64 x 64 x 100 nodes
+// 6.9 and 11.6, 100 x 70 x 60 7.1 and 11.2, 128 x 128 x 120 16.9 and 11.3,
+// 181 x 134 x 97 21.9 and 12.9, 40 x 300 x 200 24.0 and 13.9, 200 x 200 x 99
+// 32.3 and 15.7; with four rows per thread 14.2, 14.4, 14.0 and 16.5 on the
+// last four, but 39.7 instead of 43.9 on 256 x 256 x 200.  Not when the caller
+// sets a one-step tile option, and not when the final fields are asked for and
+// the collection criterion may end the run (stop_tol > 0): a blocked pass that
+// contains the last step still computes the pass's later steps, so its fields
+// would be up to kBlockedT - 1 steps past the result's.
+bool blocked_covers(const it_chamber* ch) {
+  const int ox = 64 - 2 * kBlockedT, oy = 24 - 2 * kBlockedT;
+  const double tiles = (double)((ch->nx + ox - 1) / ox) * ((ch->ny + oy - 1) / oy);
+  return (double)ch->nx * ch->ny >= 0.5 * tiles * ox * oy;
+}
+
+double interior_nodes(const it_chamber* ch) { return (double)ch->nx * ch->ny * (double)(ch->nz - 1); }
+
+int auto_steps(const it_chamber* ch, const it_exec* ex, bool fields) {
+  if (fields && ch->stop_tol > 0.0) return 1;
   if (ex && (ex->tile_x || ex->tile_y || ex->z_chunk)) return 1;
-  const double nodes = (double)ch->nx * ch->ny * (double)(ch->nz - 1);
-  if (nodes < kBlockedMinNodes || ch->nx < 64 || ch->ny < 32) return 1;
+  if (interior_nodes(ch) < kBlockedMinNodes || !blocked_covers(ch)) return 1;
   return kBlockedT;
 }
 
+// Rows per thread of a single chamber's blocked passes.
+int run_rows(const it_chamber* ch, int T, int tile_y) {
+  if (T == kBlockedT && tile_y == 0 && interior_nodes(ch) < kBlockedTallNodes) return 3;
+  return blocked_rows(T, tile_y);
+}
+
 // Steps per launch of a run.
-int exec_steps(const it_chamber* ch, const it_exec* ex, bool exact_fields) {
+int exec_steps(const it_chamber* ch, const it_exec* ex, bool fields) {
   const int T = requested_steps(ex);
-  return T > 0 ? T : auto_steps(ch, ex, exact_fields);
+  return T > 0 ? T : auto_steps(ch, ex, fields);
 }
 
 // Host check of an execution choice (T steps per launch) for a chamber,
@@ -718,7 +737,7 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
   // closed by a reduction launch before a deposit (so that their records do
   // not count the deposit) and at the end.
   const int grid_plain = 8 * tp.per_xcd;
-  const int R = T > 1 ? blocked_rows(T, tile_y) : 0;  // rows per thread of the blocked passes
+  const int R = T > 1 ? run_rows(ch, T, tile_y) : 0;  // rows per thread of the blocked passes
   double* part_buf[2] = {partials, partials + L.partial_doubles / 2};
   bool unrecorded = false;
   int64_t unrecorded_step = 0;
@@ -1261,12 +1280,18 @@ int electron_phase(const it_chamber* ch, double dt_ion, char* ws, const Layout& 
     return IT_OK;
   }
   const int64_t check_every = 64;
+  // launch l records step l - 1 (an extra block reduces its partials, which
+  // alternate between two buffers); the last step's are reduced at the end
+  double* part_buf[2] = {p.partials, p.partials + L.partial_doubles / 2};
   for (int64_t l = 0; l < ch->max_steps; ++l) {
     for (int s3 = 0; s3 < 3; ++s3) {
       p.in[s3] = pair[l & 1][s3];
       p.out[s3] = pair[(l + 1) & 1][s3];
     }
+    p.partials = part_buf[l & 1];
+    p.prev_partials = l > 0 ? part_buf[(l - 1) & 1] : nullptr;
     HIP_TRY(launch_step3(p, stream));
+    if (l + 1 == ch->max_steps) HIP_TRY(launch_reduce3(p, stream));
     if ((l + 1) % check_every == 0 || l + 1 == ch->max_steps) {
       HIP_TRY(hipMemcpyAsync(slot, p.state, sizeof(RunState), hipMemcpyDeviceToHost, stream));
       HIP_TRY(hipStreamSynchronize(stream));
@@ -1429,6 +1454,16 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
     HIP_TRY(hipMemcpyAsync(hs.p, ws + L.off_state, sizeof(fin), hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
     fin = *hs.p;
+  }
+
+  // Fields of a run that ended early (a non-finite tally, or nothing left in
+  // flight) inside one of the passes the library chose: again, a step per
+  // launch, for the fields of the last step itself.
+  if ((d_pos_out || d_neg_out) && fin.done && T > 1 && requested_steps(exec) == 0) {
+    it_exec plain{};
+    if (exec) plain = *exec;
+    plain.kernel = IT_KERNEL_PLAIN;
+    return it_solve(ch, tracks, ntracks, &plain, d_workspace, ws_bytes, stream_, h_trace, d_pos_out, d_neg_out, out);
   }
 
   fill_result(fin, dt, limit, issued, out);

@@ -421,7 +421,7 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
     }
   }
 
-  __syncthreads();  // edge sums of the last planes
+  lds_barrier();  // edge sums of the last planes
   // block reduction of T records of kAcc slots (layout [level][slot]); the
   // tallies of columns outside the owned ones are selected away here
   double a[kAcc * T];

@@ -53,9 +53,10 @@ struct PlaneRegs {
 // add_n are given (block-uniform), a pulse of a pulse train is due at the
 // next step: those densities are added to the stored outputs after the
 // tallies of this step are taken, and beta times the largest density the
-// outputs then hold enters the run's max_beta_n, as a deposit does.
+// outputs then hold enters the run's max_beta_n, as a deposit does.  done: the
+// run has stopped (nothing is computed).
 template <int SY, bool SC, bool AB, int TX = kTX, bool PU = false>
-__device__ inline void plain_tile_step(const StepParams& p, const TileCoord t, double* partial_out,
+__device__ inline void plain_tile_step(const StepParams& p, const TileCoord t, int done, double* partial_out,
                                        const double* add_p = nullptr, const double* add_n = nullptr) {
   static_assert(TX == 64 || TX == 32, "tile width");
   constexpr int kSNT = kTX * SY;
@@ -213,6 +214,7 @@ __device__ inline void plain_tile_step(const StepParams& p, const TileCoord t, d
   r1.n = ld(in_n(k0), own);
   r2.p = ld(in_p(k0 + 1), own);  // k0 + 1 <= nz
   r2.n = ld(in_n(k0 + 1), own);
+  if (done) return;
   for (int k = k0; k < k1; k += 4) {
     plane_step(k, 0, r0, r1, r2, r3, ra, rb);
     if (k + 1 >= k1) break;
@@ -223,7 +225,7 @@ __device__ inline void plain_tile_step(const StepParams& p, const TileCoord t, d
     plane_step(k + 3, 1, r3, r0, r1, r2, rb, ra);
   }
 
-  __syncthreads();  // edge sums of the last plane
+  lds_barrier();  // edge sums of the last plane
   if (lane == 0) {  // the electrode-plane sums enter the block reduction per wave
     acc[1] = edge[ty][0];
     acc[2] = edge[ty][1];
@@ -270,7 +272,7 @@ struct PairRegs {
 };
 
 template <int SY, bool SC, bool AB>
-__device__ inline void pair_tile_step(const StepParams& p, const TileCoord t, double* partial_out) {
+__device__ inline void pair_tile_step(const StepParams& p, const TileCoord t, int done, double* partial_out) {
   constexpr int kSNT = kTX * SY;
   constexpr int TXP = 2 * kTX;        // columns of the tile
   constexpr int kLW = (TXP + 4) / 2;  // LDS row in pairs
@@ -433,6 +435,7 @@ __device__ inline void pair_tile_step(const StepParams& p, const TileCoord t, do
   r1.n = ld2(in_n(k0), own);
   r2.p = ld2(in_p(k0 + 1), own);
   r2.n = ld2(in_n(k0 + 1), own);
+  if (done) return;
   for (int k = k0; k < k1; k += 4) {
     plane_step(k, 0, r0, r1, r2, r3, ra, rb);
     if (k + 1 >= k1) break;
@@ -443,7 +446,7 @@ __device__ inline void pair_tile_step(const StepParams& p, const TileCoord t, do
     plane_step(k + 3, 1, r3, r0, r1, r2, rb, ra);
   }
 
-  __syncthreads();
+  lds_barrier();
   if (lane == 0) {
     acc[1] = edge[ty][0];
     acc[2] = edge[ty][1];

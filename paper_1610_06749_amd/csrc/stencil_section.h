@@ -242,7 +242,7 @@ __device__ __forceinline__ void section_pass(const StepParams& p, int chunk, dou
       const double s = wave_sum(acc[t][q]);
       if (lane == 0) wave_part[(w * T + t) * 5 + q] = s;
     }
-  __syncthreads();  // and the edge sums of the last planes
+  lds_barrier();  // and the edge sums of the last planes
   for (int i = tid; i < T * kAcc; i += blockDim.x) {
     const int t = i / kAcc, q = i - t * kAcc;
     double s = 0.0;
