@@ -164,6 +164,9 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
     const int gy = y0 - T + g;
     in_y[r] = !absorbing || (gy >= 0 && gy < ny);
     miss_y[r] = absorbing ? (double)((gy == 0) + (gy == ny - 1)) : 0.0;
+    // beyond an absorbing boundary: an offset outside the plane, which reads
+    // zero (a select on the loaded value waited for each load at once)
+    if (AB && !(in_x && in_y[r])) off[r] = kOutside;
   }
   const int za = 1 + tc.zc * p.zc;
   const int zb = tc.valid ? min(za + p.zc, nz) : za;
@@ -201,7 +204,7 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
   // alternate and each plane is loaded two iterations ahead, the march taking
   // two iterations per loop trip (1 % faster on the 512 x 512 x 256 grid, 2 %
   // on the 96-chamber sweep); otherwise one buffer, one plane ahead.
-  constexpr bool kTwoBuffers = T * R <= 12 && R <= 4 && !AB;
+  constexpr bool kTwoBuffers = T * R <= 12 && R <= 4 && !(AB && T * R > 9);
   constexpr int kAhead = kTwoBuffers ? 2 : 1;
   double pa[R], na[R], pb[R], nb[R];
   auto load0 = [&](int K, double (&lp)[R], double (&ln)[R]) {
@@ -212,7 +215,6 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
     for (int r = 0; r < R; ++r) {
       lp[r] = load_b64(bp, off[r]);
       ln[r] = load_b64(bn, off[r]);
-      if (AB && !(in_x && in_y[r])) lp[r] = ln[r] = 0.0;  // beyond an absorbing boundary
     }
   };
   // the zero planes' edge rows held at the start
@@ -368,7 +370,6 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
         const rsrc_t pn = plane_rsrc(add_n + (size_t)q * plane, plane_bytes);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          if (AB && !(in_x && in_y[r])) continue;  // beyond an absorbing boundary: stays zero
           np[r] += load_b64(pp, off[r]);
           nn[r] += load_b64(pn, off[r]);
           if (counted && own_y[r] && own_x) add_max = fmax(add_max, fmax(np[r], nn[r]));
