@@ -220,10 +220,11 @@ hipError_t launch_reduce_steps(const StepParams& p, int nblocks, int T, hipStrea
 hipError_t launch_batch_pass(const void* table, int ninst, int total_tiles, int tile_y, int tile_x, bool sc,
                              bool ab, bool pu, int parity, bool record_prev, int T, int R, int section_threads,
                              bool crowded, hipStream_t s);
-// The same pass (recording the previous one) as a kernel node of `graph`
-// that depends on `dep` (null: none).
-hipError_t add_batch_pass_node(hipGraph_t graph, hipGraphNode_t dep, hipGraphNode_t* node, const void* table,
-                               int ninst, int total_tiles, int tile_y, int tile_x, bool sc, bool ab, bool pu,
-                               int parity, int T, int R, int section_threads, bool crowded);
+// The same pass (recording the previous one) as a kernel node: with exec null a
+// new one of `graph` that depends on `dep` (null: none), else the parameters of
+// `node` in the instantiated graph.
+hipError_t batch_pass_node(hipGraph_t graph, hipGraphExec_t exec, hipGraphNode_t dep, hipGraphNode_t* node,
+                           const void* table, int ninst, int total_tiles, int tile_y, int tile_x, bool sc, bool ab,
+                           bool pu, int parity, int T, int R, int section_threads, bool crowded);
 
 }  // namespace it

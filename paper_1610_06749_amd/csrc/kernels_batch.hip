@@ -171,15 +171,15 @@ const void* pass_kernel(int tile_y, int tile_x, bool sc, bool ab, bool pu, int T
 
 }  // namespace
 
-hipError_t add_batch_pass_node(hipGraph_t graph, hipGraphNode_t dep, hipGraphNode_t* node, const void* table,
-                               int ninst, int total_tiles, int tile_y, int tile_x, bool sc, bool ab, bool pu,
-                               int parity, int T, int R, int section_threads, bool crowded) {
+hipError_t batch_pass_node(hipGraph_t graph, hipGraphExec_t exec, hipGraphNode_t dep, hipGraphNode_t* node,
+                           const void* table, int ninst, int total_tiles, int tile_y, int tile_x, bool sc, bool ab, bool pu,
+                           int parity, int T, int R, int section_threads, bool crowded) {
   const BatchInstance* inst = (const BatchInstance*)table;
   int per_xcd = (total_tiles + 7) / 8;
   dim3 block;
   const void* fn = pass_kernel(tile_y, tile_x, sc, ab, pu, T, R, section_threads, crowded, &block);
   if (!fn) return hipErrorInvalidValue;
-  // the node copies the argument values when it is added
+  // the node copies the argument values when it is added or set
   void* args[] = {(void*)&inst, (void*)&ninst, (void*)&total_tiles, (void*)&per_xcd, (void*)&parity};
   hipKernelNodeParams kp{};
   kp.func = const_cast<void*>(fn);
@@ -188,6 +188,7 @@ hipError_t add_batch_pass_node(hipGraph_t graph, hipGraphNode_t dep, hipGraphNod
   kp.sharedMemBytes = 0;
   kp.kernelParams = args;
   kp.extra = nullptr;
+  if (exec) return hipGraphExecKernelNodeSetParams(exec, *node, &kp);
   return hipGraphAddKernelNode(node, graph, dep ? &dep : nullptr, dep ? 1 : 0, &kp);
 }
 
