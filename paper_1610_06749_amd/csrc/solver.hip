@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "internal.h"
@@ -213,7 +214,12 @@ int compute_dt(const it_chamber* ch, const it_track* tr, int64_t n, double* dt, 
   double best = transport_dt(ch);
   const double rate = pointwise_rate(ch);
   if (ch->reaction_limit > 0.0 && rate > 0.0) {
-    const double nref = reference_density(ch, tr, n);
+    double nref;
+    try {
+      nref = reference_density(ch, tr, n);
+    } catch (const std::bad_alloc&) {
+      return IT_EINVAL;  // more tracks than host memory holds
+    }
     if (nref > 0.0) best = std::min(best, ch->reaction_limit / (rate * nref));
   }
   if (!(best < INFINITY)) return IT_ENODT;
@@ -977,10 +983,10 @@ struct Section {
 
 // Shortest chunk of the section tiles.  Their records fit the partial slots laid
 // out for blocked tiles of as many steps in chunks of kBlockedT planes.
-constexpr int kSectionMinZ = 6, kSectionMinNz = 3;
+constexpr int kSectionMinZ = 4, kSectionMinNz = 3;
 static_assert(kSectionT == kBlockedT && kSectionMinZ >= kBlockedT, "partial slots of the section tiles");
 // latency of an iteration, in issue times of one block's iteration
-constexpr double kSectionLatency = 0.8, kSectionLatencyCrowded = 1.0;
+constexpr double kSectionLatency = 1.5, kSectionLatencyCrowded = 2.0;
 
 // Blocks of w waves that share a CU with `slots` waves per SIMD (measured with
 // kernels of 160 registers: a block whose waves do not fill the SIMDs evenly
@@ -1864,9 +1870,10 @@ int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* e
   const size_t plane = (size_t)ch->nx * ch->ny * sizeof(double);
   const size_t bytes = L.field_elems * sizeof(double);
   // the caller's arrays are the first field pair (copied into the workspace if
-  // they are not aligned for every kernel)
+  // they are not aligned for every kernel, or overlap)
   double* first[2] = {d_pos, d_neg};
-  const bool own = (uintptr_t)d_pos % 16 || (uintptr_t)d_neg % 16;
+  const uintptr_t a = (uintptr_t)d_pos, b = (uintptr_t)d_neg;
+  const bool own = a % 16 || b % 16 || (a < b ? b - a : a - b) < bytes;
   for (int f = 0; f < 2; ++f) {
     if (own) {
       first[f] = (double*)(ws + L.off_field[f]);
