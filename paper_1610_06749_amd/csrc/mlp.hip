@@ -284,7 +284,8 @@ __device__ inline void wload_bwd(WFrag& f, const float* __restrict__ W) {
   }
 }
 
-// acc[st][t]: the products of the tile's activations with the wave's weights.
+// acc[st][t]: the products of the activations of S samples with the wave's
+// weights.
 template <int S>
 __device__ inline void mm_f32(const float (*in)[kActStride], const WFrag& f, float4_t (&acc)[S / 16][2]) {
   const int lane = threadIdx.x % 64;
@@ -873,7 +874,7 @@ template <int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void query_f32_kernel(
     Model md, const float* __restrict__ X, int64_t n, float spread_tol, float* mean, float* spread,
     unsigned char* fallback, int* block_count) {
-  constexpr int NS = S / 16;
+  constexpr int NH = S >= 32 ? 2 : 1, HS = S / NH;  // halves of the tile
   __shared__ float zs[S * kIn];
   __shared__ __align__(16) float act[S][kActStride];
   __shared__ float w4[kH + 1];
@@ -896,22 +897,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void q
   for (int m = 0; m < members; ++m) {
     const float* master = md.master + (size_t)m * kP;
     if (tid < kH + 1) w4[tid] = master[ow4 + tid];  // its last readers passed a barrier
-    auto put = [&](int s, float x, float y) { *(float2_t*)&act[s][o] = float2_t{x, y}; };
-    each_sample<S>(
-        [&](int, int, int s) { put(s, silu(first_layer(sp, zs, s, 0)), silu(first_layer(sp, zs, s, 1))); });
+    float4_t acc[2][HS / 16][2];
+    // the first layer of half h, and the activations of its last product
+    auto first = [&](int h) {
+      each_sample<HS>([&](int, int, int s) {
+        const int hs = h * HS + s;
+        *(float2_t*)&act[hs][o] = float2_t{silu(first_layer(sp, zs, hs, 0)), silu(first_layer(sp, zs, hs, 1))};
+      });
+    };
+    auto activate = [&](int h, const float (&b)[2]) {
+      each_sample<HS>([&](int st, int v, int s) {
+        *(float2_t*)&act[h * HS + s][o] =
+            float2_t{silu(acc[h][st][0][v] + b[0]), silu(acc[h][st][1][v] + b[1])};
+      });
+    };
+    // One half's products and the other half's activations side by side.
+    first(0);
     __syncthreads();
-    float4_t acc[NS][2];
     wload_fwd(fb, master + oW3);
-    mm_f32<S>(act, fa, acc);
-    __syncthreads();  // every wave has read the activations
-    each_sample<S>(
-        [&](int st, int v, int s) { put(s, silu(acc[st][0][v] + sp.b2[0]), silu(acc[st][1][v] + sp.b2[1])); });
+    mm_f32<HS>(act, fa, acc[0]);
+    if (NH == 2) first(NH - 1);
+    __syncthreads();
+    if (NH == 2) mm_f32<HS>(act + HS, fa, acc[NH - 1]);
+    activate(0, sp.b2);
     __syncthreads();
     if (m + 1 < members) wload_fwd(fa, master + kP + oW2);
-    mm_f32<S>(act, fb, acc);
+    mm_f32<HS>(act, fb, acc[0]);
+    if (NH == 2) activate(NH - 1, sp.b2);
     __syncthreads();
-    each_sample<S>(
-        [&](int st, int v, int s) { put(s, silu(acc[st][0][v] + sp.b3[0]), silu(acc[st][1][v] + sp.b3[1])); });
+    if (NH == 2) mm_f32<HS>(act + HS, fb, acc[NH - 1]);
+    activate(0, sp.b3);
+    if (NH == 2) {
+      __syncthreads();
+      activate(NH - 1, sp.b3);
+    }
     if (m + 1 < members) sload(master + kP, sp);
     __syncthreads();
     dots_f32<S>(act, w4, yp);
