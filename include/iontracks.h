@@ -311,7 +311,8 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks,
  * deposits (the stepping of the Appendix alone).  d_pos, d_neg: device
  * [(nz+1)*ny*nx], read and overwritten in place; their electrode planes are
  * treated as zero.  h_trace: NULL or host [nsteps][IT_TRACE_COLS].  Uses the
- * chamber's constants; ch->max_steps must be >= nsteps.  Synchronises
+ * chamber's constants; ch->max_steps must be >= nsteps.  Blocked passes step
+ * the arrays themselves (after an error their contents are undefined).  Synchronises
  * `stream`.  Errors: IT_EINVAL, IT_EWORKSPACE, IT_EHIP. */
 int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* exec,
                double* d_pos, double* d_neg, void* d_workspace, size_t ws_bytes,
@@ -334,10 +335,12 @@ int it_workspace_size_batch(const it_chamber* ch, const int64_t* track_offsets, 
  * the step before it.  A pass of T steps takes at most one pulse: with a
  * train whose period is shorter than T steps the library's choice is one
  * step per pass (a request for blocked passes then returns IT_ENOTSUP;
- * it_workspace_size_batch covers both).  Each pass is one launch over the
+ * it_workspace_size_batch covers both).  Where every chamber is narrow,
+ * periodic and without space charge, the library's choice gives a block the
+ * whole cross-section instead of a tile.  Each pass is one launch over the
  * tiles of all running instances, plus one block per instance that records
  * the instance's previous step; the library
- * captures exec->check_every passes (default 32, rounded up to even) in a
+ * holds exec->check_every passes (default 32, rounded up to even) in a
  * HIP graph and replays it on `stream` until every instance has stopped.
  * out: host [ninst].  No per-step traces or fields are kept.
  * Synchronises `stream`.  Errors: IT_EINVAL, IT_ENODT, IT_ENOTSUP,
