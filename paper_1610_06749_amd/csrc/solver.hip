@@ -294,7 +294,7 @@ struct Tiling {
 
 // Tiling of the interior: tile_x x tile_y columns by chunks of z planes.
 // The stepping kernel marches 32 planes per block (down to 4 on small grids,
-// to keep several hundred blocks); the deposit kernel aims at ~2048 blocks.
+// to keep several hundred blocks).
 Tiling make_tiling(int nx, int ny, int nz, int tile_y, int zc, int tile_x = 64) {
   Tiling t;
   const int nint = nz - 1;
