@@ -152,14 +152,18 @@ __device__ inline BaseArgs base_args(const Header& H, const float* x) {
   return a;
 }
 
-// Part `part` of the weighted sum, of `parts` equal ones.
-__device__ inline double base_part(const Header& H, const BaseArgs& a, int part, int parts) {
-  const int len = kGL / parts;
+constexpr int kBaseParts = 4, kPartLen = kGL / kBaseParts;
+
+// Value of the integrand at node q.
+__device__ inline double base_node(const Header& H, const BaseArgs& a, int q) {
+  const double w = 0.5 * a.upper * (H.gl_x[q] + 1.0);
+  return exp(a.y1 * expm1(w));
+}
+
+// Part `part` of the weighted sum.
+__device__ inline double base_part(const Header& H, const BaseArgs& a, int part) {
   double s = 0.0;
-  for (int q = part * len; q < (part + 1) * len; ++q) {
-    const double w = 0.5 * a.upper * (H.gl_x[q] + 1.0);
-    s += H.gl_w[q] * exp(a.y1 * expm1(w));
-  }
+  for (int q = part * kPartLen; q < (part + 1) * kPartLen; ++q) s = fma(H.gl_w[q], base_node(H, a, q), s);
   return s;
 }
 
@@ -173,33 +177,55 @@ __device__ inline double base_finish(const Header& H, const float* x, const Base
 
 __device__ double baseline(const Header& H, const float* x) {
   const BaseArgs a = base_args(H, x);
-  double s = base_part(H, a, 0, 4);
-  for (int p = 1; p < 4; ++p) s += base_part(H, a, p, 4);
+  double s = base_part(H, a, 0);
+  for (int p = 1; p < kBaseParts; ++p) s += base_part(H, a, p);
   return base_finish(H, x, a, s);
 }
 
 // Baseline of the S samples of a tile: the block's 256 threads share the
 // quadratures (an exponential of FP64 takes as long as dozens of the network's
-// instructions), thread p S + s sums part p of sample s0 + s into part[p][s];
-// after a barrier thread s < S calls base_of, which adds its sample's parts.
+// instructions).  Thread p S + s takes the p-th share of the nodes of sample
+// s0 + s into v[.][s]: the sum of a part where four threads share a sample,
+// the integrand's values where more do.  After a barrier thread s < S calls
+// base_of, which adds its sample's sums.  Either way they are the sums of
+// baseline(), term by term, so that a sample's baseline does not depend on
+// the tile it is in.
 template <int S>
-constexpr int kBaseParts = 256 / S;
+constexpr int kBaseRows = 256 / S == kBaseParts ? kBaseParts : kGL;
 
 template <int S>
 __device__ inline void base_parts(const Header& H, const float* __restrict__ X, int64_t n, int64_t s0,
-                                  double (*part)[S]) {
+                                  double (*v)[S]) {
+  constexpr int kShare = kGL * S / 256;  // nodes of a thread
   const int p = threadIdx.x / S, s = threadIdx.x % S;
   const int64_t gs = s0 + s;
-  if (H.use_baseline && gs < n) part[p][s] = base_part(H, base_args(H, X + gs * kIn), p, kBaseParts<S>);
+  if (!H.use_baseline || gs >= n) return;
+  const BaseArgs a = base_args(H, X + gs * kIn);
+  if constexpr (kBaseRows<S> == kBaseParts) {
+    v[p][s] = base_part(H, a, p);
+  } else {
+    for (int q = p * kShare; q < (p + 1) * kShare; ++q) v[q][s] = base_node(H, a, q);
+  }
 }
 
 template <int S>
-__device__ inline double base_of(const Header& H, const float* __restrict__ X, int64_t gs, const double (*part)[S],
+__device__ inline double base_of(const Header& H, const float* __restrict__ X, int64_t gs, const double (*v)[S],
                                  int s) {
   if (!H.use_baseline) return 0.0;
   const float* x = X + gs * kIn;
-  double sum = part[0][s];
-  for (int p = 1; p < kBaseParts<S>; ++p) sum += part[p][s];
+  double part[kBaseParts];
+  if constexpr (kBaseRows<S> == kBaseParts) {
+    for (int p = 0; p < kBaseParts; ++p) part[p] = v[p][s];
+  } else {
+    for (int p = 0; p < kBaseParts; ++p) part[p] = 0.0;
+    for (int q = 0; q < kPartLen; ++q)
+      for (int p = 0; p < kBaseParts; ++p) {
+        const int node = p * kPartLen + q;
+        part[p] = fma(H.gl_w[node], v[node][s], part[p]);
+      }
+  }
+  double sum = part[0];
+  for (int p = 1; p < kBaseParts; ++p) sum += part[p];
   return base_finish(H, x, base_args(H, x), sum);
 }
 
@@ -391,7 +417,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   __shared__ float w4[kH + 1];
   __shared__ float yp[4][S];
   __shared__ float dys[S];
-  __shared__ double bp[kBaseParts<S>][S];
+  __shared__ double bp[kBaseRows<S>][S];
   const Header& H = *md.hdr;
   const int tid = threadIdx.x;
   const int m = blockIdx.y;
@@ -880,7 +906,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void q
   __shared__ float w4[kH + 1];
   __shared__ float yp[4][S];
   __shared__ float ys[S], ymin[S], ymax[S], ysum[S];
-  __shared__ double bp[kBaseParts<S>][S];
+  __shared__ double bp[kBaseRows<S>][S];
   __shared__ int cnt;
   const Header& H = *md.hdr;
   if (H.precision != IT_MLP_FP32) return;
@@ -947,7 +973,7 @@ __global__ __launch_bounds__(256) void query_bf16_kernel(Model md, const float* 
   __shared__ float zs[kTileS * kIn];
   __shared__ unsigned short act[2][kTileS][kActStride];
   __shared__ float ys[kTileS], ymin[kTileS], ymax[kTileS], ysum[kTileS];
-  __shared__ double bp[kBaseParts<kTileS>][kTileS];
+  __shared__ double bp[kBaseRows<kTileS>][kTileS];
   __shared__ int cnt;
   const Header& H = *md.hdr;
   if (H.precision != IT_MLP_BF16) return;

@@ -52,3 +52,26 @@ def test_query_at_tile_edges(gpu, n, precision):  # noqa: F811
         ys, _ = ref_forward(params, Q[-k:], norm, 3, cast=False)
         ref = ys.mean(axis=0)
         assert np.max(np.abs(mean.cpu().numpy()[-k:] - ref) / (1 + np.abs(ref))) < 2e-5
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_an_answer_does_not_depend_on_the_call(gpu, precision):  # noqa: F811
+    """The same queries in calls of other sizes (other tiles), and alone, have
+    the same answers bit for bit, with the analytic baseline in them."""
+    import torch
+    from paper_1610_06749_amd import surrogate
+    X = W.surrogate_inputs(5, 9000).astype(np.float32)
+    X[::2, [0, 4]] *= np.float32(1e-7)  # a baseline of 1e-8, which shows the order of its sums
+    norm = make_norm(X.astype(np.float64), np.linspace(0.0, 1e-3, 9000))
+    prec = gpu.IT_MLP_FP32 if precision == "fp32" else gpu.IT_MLP_BF16
+    Q = torch.tensor(X, device="cuda")
+    norm[24] = 0.0
+    for t_sigma in (1e-30, 0.1):  # the baseline alone, and the network with it
+        norm[25] = t_sigma
+        model = torch.empty(gpu.it_mlp_model_bytes(3), dtype=torch.uint8, device="cuda")
+        gpu.it_mlp_init(model, 3, W.mlp_init(7, 3), norm, phys=surrogate.phys_constants(), precision=prec)
+        mean, spread, fb, _, _ = gpu.it_mlp_query(model, Q, 1e-3)
+        for first, n in ((0, 8192), (8000, 1000), (17, 100), (8999, 1)):
+            few = gpu.it_mlp_query(model, Q[first:first + n].contiguous(), 1e-3)
+            for a, b in zip(few[:3], (mean, spread, fb)):
+                assert torch.equal(a, b[first:first + n]), (t_sigma, first, n)
