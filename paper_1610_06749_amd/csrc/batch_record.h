@@ -35,7 +35,10 @@ __device__ inline void record_previous(const BatchInstance& bi, int parity, int 
   __shared__ RunState now;
   snapshot_state(p.state, &now);
   __syncthreads();
-  if (now.done) return;
+  if (now.done) {
+    if (threadIdx.x == 0 && threadIdx.y == 0) stop_after(p.state->stop, parity);
+    return;
+  }
   // the previous pass's tile count, which its own recording block stored
   // (the host may have re-tiled the running instances since)
   __shared__ double totals[kAcc * kMaxT];
@@ -64,6 +67,7 @@ __device__ inline void record_previous(const BatchInstance& bi, int parity, int 
       st->done = 1;
       st->by_limit = 1;
     }
+    if (st->done) stop_after(st->stop, parity);
     st->rec_ntiles = bi.ntiles;  // this pass's tiles, for the next recording block
     if (train) {
       // the next pass computes steps c1 .. c1 + T - 1; a pulse at or past

@@ -22,9 +22,12 @@ __device__ void record_previous_pass(const StepParams& p) {
   __shared__ double totals[kAcc * kMaxT];
   snapshot_state(p.state, &now);
   reduce_partials<kBNT>(p.prev_partials, p.prev_nblocks, kAcc * p.prev_T, kAcc * p.prev_T, totals);
-  if (!now.done && threadIdx.x == 0 && threadIdx.y == 0)
-    finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
-                   p.min_stop_step);
+  if (threadIdx.x == 0 && threadIdx.y == 0) {
+    if (!now.done)
+      finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
+                     p.min_stop_step);
+    if (p.state->done) stop_after(p.state->stop, p.parity);
+  }
 }
 
 // SC: with the space-charge term (two more tallies per level); AB: absorbing

@@ -26,7 +26,11 @@ __device__ inline void record_step3(const Step3Params& p, const double* partials
   __shared__ double tot[kAcc3];
   snapshot_state(p.state, &now);
   reduce_partials(partials, nblocks, kAcc3, kAcc3, tot);
-  if (now.e_done || threadIdx.x != 0 || threadIdx.y != 0) return;
+  if (threadIdx.x != 0 || threadIdx.y != 0) return;
+  if (now.e_done) {
+    stop_after(p.state->e_stop, p.parity);
+    return;
+  }
   RunState& st = now;
   const double dV = p.dV;
   const double col[6] = {p.co[0].azp * tot[2] * dV, p.co[0].azm * tot[3] * dV, p.co[1].azp * tot[4] * dV,
@@ -46,9 +50,11 @@ __device__ inline void record_step3(const Step3Params& p, const double* partials
     st.flags |= IT_FLAG_NONFINITE;
     st.e_done = 1;
     st.done = 1;
+    stop_now(st.stop);  // no ion kernel is running
   } else if (tot[13] * dV <= p.stop_tol * st.released_e) {
     st.e_done = 1;
   }
+  if (st.e_done) stop_after(st.e_stop, p.parity);
   *p.state = st;
 }
 
@@ -66,7 +72,7 @@ __global__ __launch_bounds__(kNT3) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     record_step3(p, p.prev_partials, (int)gridDim.x - 1);
     return;
   }
-  if (p.state->e_done) return;
+  if (launch_skips(p.state->e_stop, p.parity)) return;
   __shared__ double sl[2][3][kTY3 + 2][kTX3 + 2];
   __shared__ double lds[(kNT3 / kWave) * kAcc3];
   double acc[kAcc3];

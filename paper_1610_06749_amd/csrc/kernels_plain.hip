@@ -23,9 +23,9 @@ namespace it {
 // block sums the previous step's partials in a fixed order and records the
 // step (finalize_steps), while the others compute this step.  The kernel
 // boundary before this launch makes the previous partials visible; the
-// state it writes is read by the next launch.  Stepping blocks that read
-// `done` while it is being set only decide whether to compute a step past
-// the stop, whose output goes to the field pair not holding the stop step.
+// state it writes is read by the next launch.  Once it finds the run stopped,
+// this launch has computed a step past the stop, whose output goes to the field
+// pair not holding the stop step; the launches after it skip (see StopFlags).
 // Tiles of column pairs aim at 8 waves per CU, so they may use more
 // registers (at least 2 waves per SIMD instead of 4).
 template <int SY, bool SC, bool AB, int TX>
@@ -35,14 +35,17 @@ __global__ __launch_bounds__(kTX * SY) __attribute__((amdgpu_waves_per_eu(TX == 
     __shared__ double totals[kAcc * kMaxT];
     snapshot_state(p.state, &now);
     reduce_partials<kTX * SY>(p.prev_partials, p.prev_nblocks, kAcc * p.prev_T, kAcc * p.prev_T, totals);
-    if (!now.done && threadIdx.x == 0 && threadIdx.y == 0)
-      finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
-                     p.min_stop_step);
+    if (threadIdx.x == 0 && threadIdx.y == 0) {
+      if (!now.done)
+        finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
+                       p.min_stop_step);
+      if (p.state->done) stop_after(p.state->stop, p.parity);
+    }
     return;
   }
   // set by an earlier launch: every block skips (read here, looked at once the
   // first planes are on their way)
-  const int done = p.state->done;
+  const bool done = launch_skips(p.state->stop, p.parity);
   const TileCoord t = decode_tile(p.tiles_x, p.tiles_y, p.ntiles, p.per_xcd);
   if constexpr (TX == 2 * kTX)
     pair_tile_step<SY, SC, AB>(p, t, done, p.partials + (size_t)blockIdx.x * kAcc);
@@ -55,12 +58,16 @@ __global__ __launch_bounds__(kTX * SY) __attribute__((amdgpu_waves_per_eu(TX == 
 // Running as its own launch, it sees every partial without device-wide
 // fences in the stepping kernel.
 __global__ __launch_bounds__(1024) void reduce_steps_kernel(StepParams p, int nblocks, int T) {
-  if (p.state->done) return;
+  __shared__ RunState now;
   __shared__ double totals[kAcc * kMaxT];
+  snapshot_state(p.state, &now);
   reduce_partials<1024>(p.partials, nblocks, kAcc * T, kAcc * T, totals);
-  if (threadIdx.x == 0)
-    finalize_steps(p.state, p.state, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol,
-                   p.min_stop_step);
+  if (threadIdx.x == 0) {
+    if (!now.done)
+      finalize_steps(p.state, &now, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol,
+                     p.min_stop_step);
+    if (p.state->done) stop_now(p.state->stop);
+  }
 }
 
 hipError_t launch_reduce_steps(const StepParams& p, int nblocks, int T, hipStream_t s) {

@@ -689,6 +689,7 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
   sp.partials = partials;
   sp.state = state;
   sp.trace = trace;
+  sp.parity = 0;
   sp.prev_partials = nullptr;
   sp.prev_nblocks = 0;
   sp.prev_T = 1;
@@ -781,6 +782,7 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
     // this launch's partials, and the previous launch's for its extra block
     const int buf = issued & 1;
     sp.partials = part_buf[buf];
+    sp.parity = buf;
     sp.prev_partials = unrecorded ? part_buf[unrecorded_buf] : nullptr;
     sp.prev_nblocks = unrecorded_blocks;
     sp.prev_T = unrecorded_T;
@@ -1295,6 +1297,7 @@ int electron_phase(const it_chamber* ch, double dt_ion, char* ws, const Layout& 
       p.out[s3] = pair[(l + 1) & 1][s3];
     }
     p.partials = part_buf[l & 1];
+    p.parity = (int)(l & 1);
     p.prev_partials = l > 0 ? part_buf[(l - 1) & 1] : nullptr;
     HIP_TRY(launch_step3(p, stream));
     if (l + 1 == ch->max_steps) HIP_TRY(launch_reduce3(p, stream));
@@ -1637,6 +1640,7 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
       sp.step0 = 0;
       sp.min_stop_step = train ? INT64_MAX : 0;  // a pulse train ends with its last period
       sp.partials = (double*)(ws + L.off_partials) + (size_t)par * L.slots * kAcc * T;
+      sp.parity = par;
       sp.state = states + q;
       sp.trace = nullptr;
     }

@@ -56,7 +56,7 @@ struct PlaneRegs {
 // outputs then hold enters the run's max_beta_n, as a deposit does.  done: the
 // run has stopped (nothing is computed).
 template <int SY, bool SC, bool AB, int TX = kTX, bool PU = false>
-__device__ inline void plain_tile_step(const StepParams& p, const TileCoord t, int done, double* partial_out,
+__device__ inline void plain_tile_step(const StepParams& p, const TileCoord t, bool done, double* partial_out,
                                        const double* add_p = nullptr, const double* add_n = nullptr) {
   static_assert(TX == 64 || TX == 32, "tile width");
   constexpr int kSNT = kTX * SY;
@@ -272,7 +272,7 @@ struct PairRegs {
 };
 
 template <int SY, bool SC, bool AB>
-__device__ inline void pair_tile_step(const StepParams& p, const TileCoord t, int done, double* partial_out) {
+__device__ inline void pair_tile_step(const StepParams& p, const TileCoord t, bool done, double* partial_out) {
   constexpr int kSNT = kTX * SY;
   constexpr int TXP = 2 * kTX;        // columns of the tile
   constexpr int kLW = (TXP + 4) / 2;  // LDS row in pairs

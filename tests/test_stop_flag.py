@@ -1,0 +1,70 @@
+"""The stop flag of launches that record the launch before them: whenever the
+waves of a launch look at it, before or after their own launch's recording
+block has set it, they decide alike, and every launch after that one skips.
+The header the kernels include, compiled for the CPU and driven through all
+positions of the recording block among its launch's waves."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1610_06749_amd", "csrc")
+
+HARNESS = r"""
+#include <cstdio>
+#include "stop_flag.h"
+using namespace it;
+// Launches 0, 1, ... of alternating parity; launch l records launch l - 1,
+// whose step ends the run if it is `last`, and its recording block acts after
+// `at` of its `waves` waves have looked.  With close >= 0 a launch without
+// tile blocks records launch `close` before launch close + 1, which then has
+// no recording block.
+static int run(int last, int first_parity, int at, int waves, int close) {
+  StopFlags f = {{0, 0}};
+  bool done = false;
+  for (int l = 0; l < last + 8; ++l) {
+    const int parity = (l + first_parity) & 1;
+    int skipped = 0;
+    for (int w = 0; w <= waves; ++w) {
+      if (w == at && l > 0 && l - 1 != close) {
+        if (l - 1 == last) done = true;
+        if (done) stop_after(f, parity);
+      }
+      if (w < waves) skipped += launch_skips(f, parity);
+    }
+    if (skipped != 0 && skipped != waves) return 1;  // the waves disagree
+    // launch last + 1 steps past the stop, unless a closing launch came before it
+    const int until = close == last ? last : last + 1;
+    if ((skipped == waves) != (l > until)) return 2;
+    if (l == close) {
+      if (l == last) done = true;
+      if (done) stop_now(f);
+    }
+  }
+  return 0;
+}
+int main() {
+  for (int last = 0; last < 5; ++last)
+    for (int parity = 0; parity < 2; ++parity)
+      for (int at = 0; at <= 4; ++at)
+        for (int close = -1; close < 9; ++close)
+          if (int bad = run(last, parity, at, 4, close)) {
+            std::printf("last %d parity %d at %d close %d: %d\n", last, parity, at, close, bad);
+            return 1;
+          }
+  return 0;
+}
+"""
+
+
+def test_waves_of_a_launch_decide_alike(tmp_path):
+    cxx = shutil.which("g++")
+    if not cxx:
+        pytest.skip("no host compiler")
+    src = tmp_path / "harness.cpp"
+    src.write_text(HARNESS)
+    exe = str(tmp_path / "harness")
+    subprocess.check_call([cxx, "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", exe])
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
