@@ -311,8 +311,7 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks,
  * deposits (the stepping of the Appendix alone).  d_pos, d_neg: device
  * [(nz+1)*ny*nx], read and overwritten in place; their electrode planes are
  * treated as zero.  h_trace: NULL or host [nsteps][IT_TRACE_COLS].  Uses the
- * chamber's constants; ch->max_steps must be >= nsteps.  Blocked passes step
- * the arrays themselves (after an error their contents are undefined).  Synchronises
+ * chamber's constants; ch->max_steps must be >= nsteps.  Synchronises
  * `stream`.  Errors: IT_EINVAL, IT_EWORKSPACE, IT_EHIP. */
 int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* exec,
                double* d_pos, double* d_neg, void* d_workspace, size_t ws_bytes,

@@ -212,6 +212,9 @@ hipError_t launch_step_plain(const StepParams& p, int tile_y, int tile_x, hipStr
 hipError_t launch_deposit(const DepositParams& p, hipStream_t s);
 // The first deposits of n chambers (device table), `tiles` tiles in all.
 hipError_t launch_deposit_batch(const DepositParams* table, int n, int tiles, hipStream_t s);
+// Zeros the electrode planes (0 and nz) of two field pairs of `plane` nodes a plane.
+hipError_t launch_zero_electrodes(double* const (&pair0)[2], double* const (&pair1)[2], size_t plane, int nz,
+                                  hipStream_t s);
 hipError_t launch_reduce_steps(const StepParams& p, int nblocks, int T, hipStream_t s);
 // sc: some instance has the space-charge term on; ab: some instance has
 // absorbing lateral boundaries; pu: some instance has a pulse train (one

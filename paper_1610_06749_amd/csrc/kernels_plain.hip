@@ -15,6 +15,8 @@
 // this launch, and keeping them out of L2 leaves it to the reused inputs.
 // No MFMA: the update is a 7-point stencil, not a contraction, and the
 // kernel is bound by HBM bandwidth (32 bytes per node and step).
+#include <algorithm>
+
 #include "stencil_plain.h"
 
 namespace it {
@@ -72,6 +74,26 @@ __global__ __launch_bounds__(1024) void reduce_steps_kernel(StepParams p, int nb
 
 hipError_t launch_reduce_steps(const StepParams& p, int nblocks, int T, hipStream_t s) {
   hipLaunchKernelGGL(reduce_steps_kernel, dim3(1), dim3(1024), 0, s, p, nblocks, T);
+  return hipGetLastError();
+}
+
+namespace {
+
+__global__ __launch_bounds__(256) void zero_electrodes_kernel(double* a, double* b, double* c, double* d, size_t plane,
+                                                              size_t top) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < plane; i += (size_t)gridDim.x * 256) {
+    a[i] = b[i] = c[i] = d[i] = 0.0;
+    a[top + i] = b[top + i] = c[top + i] = d[top + i] = 0.0;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_zero_electrodes(double* const (&pair0)[2], double* const (&pair1)[2], size_t plane, int nz,
+                                  hipStream_t s) {
+  const unsigned grid = (unsigned)std::min<size_t>((plane + 255) / 256, 2048);
+  hipLaunchKernelGGL(zero_electrodes_kernel, dim3(grid), dim3(256), 0, s, pair0[0], pair0[1], pair1[0], pair1[1], plane,
+                     plane * nz);
   return hipGetLastError();
 }
 

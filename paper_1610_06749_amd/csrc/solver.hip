@@ -639,9 +639,11 @@ struct Event {
 // up to T steps, cut at deposit steps, and reads the run state back every
 // `check_every` steps (two checks in flight) to stop once the device has
 // flagged completion.
-// pos0, neg0: the first field pair (the workspace's, or a caller's own).
-int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const Layout& L, double* pos0,
-             double* neg0, const std::vector<Event>& events, int same_r,
+// io: null, or a field pair that the first launch reads instead of the
+// workspace's and the last launch writes, if it is not the first too; the pairs
+// between are the workspace's (no events then).
+int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const Layout& L, double* const* io,
+             const std::vector<Event>& events, int same_r,
              int64_t nsteps, int64_t min_stop_step, double stop_tol, int T, hipStream_t stream, HostSlots& hs,
              RunState* final_state, int* passes_issued) {
   const int exec_rc = check_exec(ch, ex, T);
@@ -651,7 +653,8 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
   const bool span = ex && ex->timing_events && ex->timing_span && ex->n_timing_events >= 2;
   const int n_timing = ex && ex->timing_events && !span ? std::max(ex->n_timing_events, 0) / 2 : 0;
 
-  double* field[4] = {pos0, neg0, (double*)(ws + L.off_field[2]), (double*)(ws + L.off_field[3])};
+  double* field[4];
+  for (int f = 0; f < 4; ++f) field[f] = (double*)(ws + L.off_field[f]);
   double* partials = (double*)(ws + L.off_partials);
   RunState* state = (RunState*)(ws + L.off_state);
   DepTrack* tracks = (DepTrack*)(ws + L.off_tracks);
@@ -774,10 +777,12 @@ int run_loop(const it_chamber* ch, double dt, const it_exec* ex, char* ws, const
     }
     const int64_t next_dep = ev < events.size() ? events[ev].step : nsteps;
     const int64_t todo = std::min<int64_t>(std::min<int64_t>(T, next_dep - l), nsteps - l);
-    sp.pin = field[2 * cur];
-    sp.nin = field[2 * cur + 1];
-    sp.pout = field[2 * (1 - cur)];
-    sp.nout = field[2 * (1 - cur) + 1];
+    double* const* in = io && l == 0 ? io : field + 2 * cur;
+    double* const* out = io && l > 0 && l + todo == nsteps ? io : field + 2 * (1 - cur);
+    sp.pin = in[0];
+    sp.nin = in[1];
+    sp.pout = out[0];
+    sp.nout = out[1];
     sp.step0 = l;
     // this launch's partials, and the previous launch's for its extra block
     const int buf = issued & 1;
@@ -1456,8 +1461,8 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
   const int64_t ion_steps = train ? std::min<int64_t>(ch->n_pulses * period_steps, limit) : limit;
   const int64_t min_stop = train ? INT64_MAX : std::max<int64_t>(last_dep, 0);
   if (ion_steps > 0) {
-    rc = run_loop(ch, dt, exec, ws, L, (double*)(ws + L.off_field[0]), (double*)(ws + L.off_field[1]), events,
-                  same_radii(tracks, ntracks), ion_steps, min_stop, ch->stop_tol, T, stream, hs, &fin, &issued);
+    rc = run_loop(ch, dt, exec, ws, L, nullptr, events, same_radii(tracks, ntracks), ion_steps, min_stop,
+                  ch->stop_tol, T, stream, hs, &fin, &issued);
     if (rc) return rc;
   } else {
     HIP_TRY(hipMemcpyAsync(hs.p, ws + L.off_state, sizeof(fin), hipMemcpyDeviceToHost, stream));
@@ -1871,25 +1876,28 @@ int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* e
   if (nsteps == 0) return IT_OK;
   hipStream_t stream = (hipStream_t)stream_;
   char* ws = (char*)d_workspace;
-  const size_t plane = (size_t)ch->nx * ch->ny * sizeof(double);
   const size_t bytes = L.field_elems * sizeof(double);
-  // With blocked passes the caller's arrays are the first field pair (copied
-  // into the workspace if they are not aligned for every kernel, or overlap).
-  // Not a step per launch, which streams at the memory's rate: four arrays that
-  // all begin on a large power of two took 408 us per step on 512 x 512 x 256
-  // nodes, the workspace's 371 (blocked passes 181.7 and 185.5).
-  double* first[2] = {d_pos, d_neg};
-  const uintptr_t a = (uintptr_t)d_pos, b = (uintptr_t)d_neg;
-  const bool own = T == 1 || a % 16 || b % 16 || (a < b ? b - a : a - b) < bytes;
-  for (int f = 0; f < 2; ++f) {
-    if (own) {
-      first[f] = (double*)(ws + L.off_field[f]);
-      HIP_TRY(hipMemcpyAsync(first[f], f ? d_neg : d_pos, bytes, hipMemcpyDeviceToDevice, stream));
-    }
-    // electrode planes are zero by definition, in both pairs
-    HIP_TRY(hipMemset2DAsync(first[f], (size_t)ch->nz * plane, 0, plane, 2, stream));
-    HIP_TRY(hipMemset2DAsync(ws + L.off_field[2 + f], (size_t)ch->nz * plane, 0, plane, 2, stream));
-  }
+  // The first launch reads the caller's arrays and the last one writes them, so
+  // that they are not copied and yet are as they were if the call fails before
+  // its last launch (48 steps on 512 x 512 x 256 nodes 170 us each, 176 with the
+  // passes stepping the arrays in place; a step per launch 371, 391 with copies
+  // into and out of the workspace).  Copied if they are not aligned for every
+  // kernel, or overlap each other or the workspace.
+  double* caller[2] = {d_pos, d_neg};
+  double* pair0[2] = {(double*)(ws + L.off_field[0]), (double*)(ws + L.off_field[1])};
+  double* pair1[2] = {(double*)(ws + L.off_field[2]), (double*)(ws + L.off_field[3])};
+  auto apart = [&](const void* p, const void* q, size_t q_bytes) {
+    const uintptr_t a = (uintptr_t)p, b = (uintptr_t)q;
+    return a + bytes <= b || b + q_bytes <= a;
+  };
+  const bool direct = (uintptr_t)d_pos % 16 == 0 && (uintptr_t)d_neg % 16 == 0 &&
+                      apart(d_pos, d_neg, bytes) && apart(d_pos, ws, L.total) && apart(d_neg, ws, L.total);
+  if (!direct)
+    for (int f = 0; f < 2; ++f)
+      HIP_TRY(hipMemcpyAsync(pair0[f], caller[f], bytes, hipMemcpyDeviceToDevice, stream));
+  // electrode planes are zero by definition, in every pair
+  HIP_TRY(launch_zero_electrodes(pair0, pair1, (size_t)ch->nx * ch->ny, ch->nz, stream));
+  if (direct) HIP_TRY(launch_zero_electrodes(caller, caller, (size_t)ch->nx * ch->ny, ch->nz, stream));
   const RunState init = initial_run_state();
   HIP_TRY(hipMemcpyAsync(ws + L.off_state, &init, sizeof(init), hipMemcpyHostToDevice, stream));
   std::vector<Event> none;
@@ -1897,13 +1905,14 @@ int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* e
   int issued = 0;
   HostSlots hs;
   host_slots(exec, 1, hs);
-  rc = run_loop(ch, dt, exec, ws, L, first[0], first[1], none, 1, nsteps, INT64_MAX, 0.0, T, stream, hs, &fin, &issued);
+  rc = run_loop(ch, dt, exec, ws, L, direct ? caller : nullptr, none, 1, nsteps, INT64_MAX, 0.0, T, stream, hs, &fin,
+                &issued);
   if (rc) return rc;
-  const double* last[2] = {first[0], first[1]};
-  if (fin.passes & 1)
-    for (int f = 0; f < 2; ++f) last[f] = (const double*)(ws + L.off_field[2 + f]);
-  if (last[0] != d_pos) HIP_TRY(hipMemcpyAsync(d_pos, last[0], bytes, hipMemcpyDeviceToDevice, stream));
-  if (last[1] != d_neg) HIP_TRY(hipMemcpyAsync(d_neg, last[1], bytes, hipMemcpyDeviceToDevice, stream));
+  // the last launch wrote the caller's arrays unless it was the first too, or
+  // came after the step that ended the run (a non-finite tally)
+  if (!direct || issued == 1 || fin.passes < issued)
+    for (int f = 0; f < 2; ++f)
+      HIP_TRY(hipMemcpyAsync(caller[f], fin.passes & 1 ? pair1[f] : pair0[f], bytes, hipMemcpyDeviceToDevice, stream));
   if (h_trace)
     HIP_TRY(hipMemcpyAsync(h_trace, ws + L.off_trace, (size_t)nsteps * IT_TRACE_COLS * sizeof(double),
                            hipMemcpyDeviceToHost, stream));
