@@ -34,9 +34,11 @@
  *     unrelated HIP call left there is not taken for one of theirs;
  *   - the caller owns every buffer.  "host" pointers are ordinary CPU memory,
  *     "device" pointers are HIP device memory of the current device.  The
- *     library allocates no memory, device or host: scratch space comes from
+ *     library allocates no device memory: scratch space comes from
  *     the caller's workspace and, optionally, its page-locked host buffer
- *     (it_exec.host_buffer).  Within a call it creates and destroys HIP
+ *     (it_exec.host_buffer).  Ordinary host memory is taken only within a call
+ *     (arrays per track and per chamber; IT_EINVAL if they do not fit).  Within
+ *     a call it creates and destroys HIP
  *     events and, in it_solve_batch, one HIP graph and its executable;
  *   - device work runs on the HIP stream passed as `stream` (a hipStream_t,
  *     NULL = the default stream) and on no other stream.  Calls that return
@@ -57,7 +59,8 @@ extern "C" {
 
 /* ---- status codes ---- */
 #define IT_OK 0
-#define IT_EINVAL -1      /* invalid argument: a size, a constant or a track is out of range */
+#define IT_EINVAL -1      /* invalid argument: a size, a constant or a track is out of range, or there are more
+                           * tracks than host memory holds */
 #define IT_ENODT -2       /* neither drift nor diffusion bounds the time step (E = 0 and D = 0) */
 #define IT_EWORKSPACE -3  /* workspace NULL or smaller than it_workspace_size() */
 #define IT_EHIP -4        /* a HIP runtime call failed (no device, launch failure, ...) */

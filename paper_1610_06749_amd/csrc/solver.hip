@@ -5,7 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <new>
+#include <exception>
 #include <vector>
 
 #include "internal.h"
@@ -214,12 +214,7 @@ int compute_dt(const it_chamber* ch, const it_track* tr, int64_t n, double* dt, 
   double best = transport_dt(ch);
   const double rate = pointwise_rate(ch);
   if (ch->reaction_limit > 0.0 && rate > 0.0) {
-    double nref;
-    try {
-      nref = reference_density(ch, tr, n);
-    } catch (const std::bad_alloc&) {
-      return IT_EINVAL;  // more tracks than host memory holds
-    }
+    const double nref = reference_density(ch, tr, n);
     if (nref > 0.0) best = std::min(best, ch->reaction_limit / (rate * nref));
   }
   if (!(best < INFINITY)) return IT_ENODT;
@@ -571,6 +566,45 @@ void host_slots(const it_exec* ex, int ninst, HostSlots& h) {
     h.pinned = false;
   }
 }
+
+// Runs an entry point's body: host arrays that do not fit the memory there is
+// become an error code, not an exception that leaves the C ABI.
+template <class F>
+int without_exceptions(F body) {
+  try {
+    return body();
+  } catch (const std::exception&) {
+    return IT_EINVAL;
+  }
+}
+
+// Waits for the stream when a call ends early, so that no copy is left that
+// reads the call's host arrays (declare it after them).
+struct Drain {
+  hipStream_t stream;
+  bool armed = true;
+  ~Drain() {
+    if (armed) (void)hipStreamSynchronize(stream);
+  }
+};
+
+// A batch's graph of passes and the events of its read-backs.
+struct Replay {
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+  hipEvent_t evs[2] = {};
+  void release_graph() {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    if (graph) (void)hipGraphDestroy(graph);
+    exec = nullptr;
+    graph = nullptr;
+  }
+  ~Replay() {
+    release_graph();
+    for (hipEvent_t e : evs)
+      if (e) (void)hipEventDestroy(e);
+  }
+};
 
 #define HIP_TRY(expr)                               \
   do {                                              \
@@ -1239,7 +1273,7 @@ int it_dt(const it_chamber* ch, const it_track* tracks, int64_t ntracks, double*
   if (rc) return rc;
   rc = check_tracks(tracks, ntracks);
   if (rc) return rc;
-  return compute_dt(ch, tracks, ntracks, dt);
+  return without_exceptions([&] { return compute_dt(ch, tracks, ntracks, dt); });
 }
 
 int it_validate(const it_chamber* ch, const it_track* tracks, int64_t ntracks) {
@@ -1323,9 +1357,9 @@ int electron_phase(const it_chamber* ch, double dt_ion, char* ws, const Layout& 
   return IT_OK;
 }
 
-int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, const it_exec* exec,
-             void* d_workspace, size_t ws_bytes, void* stream_, double* h_trace, double* d_pos_out,
-             double* d_neg_out, it_result* out) {
+static int it_solve_body(const it_chamber* ch, const it_track* tracks, int64_t ntracks, const it_exec* exec,
+                         void* d_workspace, size_t ws_bytes, void* stream_, double* h_trace, double* d_pos_out,
+                         double* d_neg_out, it_result* out) {
   clear_stale_error();
   if (!out) return IT_EINVAL;
   int rc = check_chamber(ch);
@@ -1414,6 +1448,7 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
 
   RunState init = initial_run_state();
   if (train) init.period_step = (ch->n_pulses - 1) * period_steps;
+  Drain drain{stream};
   HIP_TRY(hipMemcpyAsync(ws + L.off_state, &init, sizeof(init), hipMemcpyHostToDevice, stream));
   if (!dev.empty())
     HIP_TRY(hipMemcpyAsync(ws + L.off_tracks, dev.data(), dev.size() * sizeof(DepTrack),
@@ -1470,6 +1505,7 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
     fin = *hs.p;
   }
 
+  drain.armed = false;  // the run's end was waited for
   // Fields of a run that ended early (a non-finite tally, or nothing left in
   // flight) inside one of the passes the library chose: again, a step per
   // launch, for the fields of the last step itself.
@@ -1477,7 +1513,8 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
     it_exec plain{};
     if (exec) plain = *exec;
     plain.kernel = IT_KERNEL_PLAIN;
-    return it_solve(ch, tracks, ntracks, &plain, d_workspace, ws_bytes, stream_, h_trace, d_pos_out, d_neg_out, out);
+    return it_solve_body(ch, tracks, ntracks, &plain, d_workspace, ws_bytes, stream_, h_trace, d_pos_out, d_neg_out,
+                         out);
   }
 
   fill_result(fin, dt, limit, issued, out);
@@ -1500,8 +1537,16 @@ int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, cons
   return IT_OK;
 }
 
-int it_workspace_size_batch(const it_chamber* ch, const int64_t* track_offsets, int32_t ninst,
-                            const it_exec* exec, size_t* bytes) {
+int it_solve(const it_chamber* ch, const it_track* tracks, int64_t ntracks, const it_exec* exec,
+             void* d_workspace, size_t ws_bytes, void* stream_, double* h_trace, double* d_pos_out,
+             double* d_neg_out, it_result* out) {
+  return without_exceptions([&] {
+    return it_solve_body(ch, tracks, ntracks, exec, d_workspace, ws_bytes, stream_, h_trace, d_pos_out, d_neg_out, out);
+  });
+}
+
+static int it_workspace_size_batch_body(const it_chamber* ch, const int64_t* track_offsets, int32_t ninst,
+                                        const it_exec* exec, size_t* bytes) {
   if (!bytes || !ch || !track_offsets || ninst < 1 || ninst > 65536) return IT_EINVAL;
   for (int q = 0; q < ninst; ++q) {
     const int rc = check_chamber(&ch[q]);
@@ -1527,9 +1572,16 @@ int it_workspace_size_batch(const it_chamber* ch, const int64_t* track_offsets, 
   return IT_OK;
 }
 
-int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_track* tracks,
-                   int32_t ninst, const it_exec* exec, void* d_workspace, size_t ws_bytes, void* stream_,
-                   it_result* out) {
+int it_workspace_size_batch(const it_chamber* ch, const int64_t* track_offsets, int32_t ninst,
+                            const it_exec* exec, size_t* bytes) {
+  return without_exceptions([&] {
+    return it_workspace_size_batch_body(ch, track_offsets, ninst, exec, bytes);
+  });
+}
+
+static int it_solve_batch_body(const it_chamber* ch, const int64_t* track_offsets, const it_track* tracks,
+                               int32_t ninst, const it_exec* exec, void* d_workspace, size_t ws_bytes,
+                               void* stream_, it_result* out) {
   clear_stale_error();
   if (!out) return IT_EINVAL;
   int rc = check_batch(ch, track_offsets, tracks, ninst);
@@ -1700,6 +1752,11 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     deposit_tiles += dp.ntiles;
   }
   static_assert(sizeof(DepositParams) <= sizeof(BatchInstance), "the deposit table lies where the step table will");
+  HostSlots hs;
+  host_slots(exec, ninst, hs);
+  RunState* host = hs.p;
+  Replay replay;
+  Drain drain{stream};
   if (!all_tracks.empty())
     HIP_TRY(hipMemcpyAsync(ws + B.off_tracks, all_tracks.data(), all_tracks.size() * sizeof(DepTrack),
                            hipMemcpyHostToDevice, stream));
@@ -1708,22 +1765,11 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
                          stream));
   HIP_TRY(launch_deposit_batch((const DepositParams*)(ws + B.off_table), ninst, deposit_tiles, stream));
   // The pass chain runs on the tile list of the running instances only: the
-  // table is rebuilt (and the graph re-captured) whenever a quarter of its
+  // table is rebuilt (and the graph's nodes set anew) whenever a quarter of its
   // instances have stopped, so finished chambers cost no dispatches.  All
   // running instances have executed the same number of passes, so they
   // share the field parity and a rebuilt table keeps the graph's pattern.
-  HostSlots hs;
-  host_slots(exec, ninst, hs);
-  RunState* host = hs.p;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec_graph = nullptr;
   std::vector<hipGraphNode_t> nodes(passes_per_graph);
-  auto release_graph = [&]() {
-    if (exec_graph) (void)hipGraphExecDestroy(exec_graph);
-    if (graph) (void)hipGraphDestroy(graph);
-    exec_graph = nullptr;
-    graph = nullptr;
-  };
   // Blocked tiles of the running instances in the chunk length that suits
   // them (a pass computed with the previous tiling is still reduced over its
   // own tiles: each recording block leaves its pass's tile count in the run
@@ -1766,18 +1812,18 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     // batch of 192 chambers rebuilds its table 18 times.
     auto chain = [&](hipGraphExec_t into) -> hipError_t {
       for (int k = 0; k < passes_per_graph; ++k) {
-        const hipError_t e = batch_pass_node(graph, into, k ? nodes[k - 1] : nullptr, &nodes[k], ws + B.off_table,
+        const hipError_t e = batch_pass_node(replay.graph, into, k ? nodes[k - 1] : nullptr, &nodes[k], ws + B.off_table,
                                              (int)t.size(), tiles, rows, tile_x, any_sc, any_ab, any_pu,
                                              (parity0 + k) & 1, T, R, sec.threads, sec.crowded);
         if (e != hipSuccess) return e;
       }
       return hipSuccess;
     };
-    if (exec_graph && chain(exec_graph) == hipSuccess) return IT_OK;
+    if (replay.exec && chain(replay.exec) == hipSuccess) return IT_OK;
     clear_stale_error();
-    release_graph();
-    if (hipGraphCreate(&graph, 0) != hipSuccess || chain(nullptr) != hipSuccess) return IT_EHIP;
-    if (hipGraphInstantiate(&exec_graph, graph, nullptr, nullptr, 0) != hipSuccess) return IT_EHIP;
+    replay.release_graph();
+    if (hipGraphCreate(&replay.graph, 0) != hipSuccess || chain(nullptr) != hipSuccess) return IT_EHIP;
+    if (hipGraphInstantiate(&replay.exec, replay.graph, nullptr, nullptr, 0) != hipSuccess) return IT_EHIP;
     return IT_OK;
   };
   // Pass p computes step p of every running instance and records step p-1
@@ -1785,38 +1831,30 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
   // a first pass that only steps primes the chain; the graph's passes
   // continue from parity 1.
   rc = build(1);
-  if (rc) {
-    release_graph();
-    return rc;
-  }
+  if (rc) return rc;
   {
     int tiles = 0;
     for (int q = 0; q < ninst; ++q) tiles += table[q].ntiles;
     if (launch_batch_pass(ws + B.off_table, ninst, tiles, rows, tile_x, any_sc, any_ab, any_pu, 0, false, T, R,
-                          sec.threads, sec.crowded, stream) !=
-        hipSuccess) {
-      release_graph();
+                          sec.threads, sec.crowded, stream) != hipSuccess)
       return IT_EHIP;
-    }
   }
   (void)total_tiles;
   // Replays until every instance has stopped; two replays in flight so the
   // GPU never idles on the read-back.
   const int64_t steps_per_replay = (int64_t)passes_per_graph * T;
   const int64_t max_replays = (max_steps_all + steps_per_replay - 1) / steps_per_replay + 1;
-  hipEvent_t evs[2];
-  HIP_TRY(hipEventCreateWithFlags(&evs[0], hipEventDisableTiming));
-  HIP_TRY(hipEventCreateWithFlags(&evs[1], hipEventDisableTiming));
+  for (hipEvent_t& e : replay.evs) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   int issued = 1;  // the priming pass
   int64_t replays_since_build = 0;
   rc = IT_OK;
   for (int64_t r = 0; r < max_replays; ++r) {
-    if (hipGraphLaunch(exec_graph, stream) != hipSuccess) { rc = IT_EHIP; break; }
+    if (hipGraphLaunch(replay.exec, stream) != hipSuccess) { rc = IT_EHIP; break; }
     issued += passes_per_graph;
     ++replays_since_build;
     RunState* slot = host + (r & 1) * ninst;
     if (hipMemcpyAsync(slot, states, (size_t)ninst * sizeof(RunState), hipMemcpyDeviceToHost, stream) != hipSuccess ||
-        hipEventRecord(evs[r & 1], stream) != hipSuccess) { rc = IT_EHIP; break; }
+        hipEventRecord(replay.evs[r & 1], stream) != hipSuccess) { rc = IT_EHIP; break; }
     if (!hs.pinned) {  // an ordinary host buffer: the copy of this replay completes first
       if (hipStreamSynchronize(stream) != hipSuccess) { rc = IT_EHIP; break; }
       bool any = false;
@@ -1825,7 +1863,7 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
     }
     if (r >= 1) {
       RunState* prev = host + ((r - 1) & 1) * ninst;
-      if (hipEventSynchronize(evs[(r - 1) & 1]) != hipSuccess) { rc = IT_EHIP; break; }
+      if (hipEventSynchronize(replay.evs[(r - 1) & 1]) != hipSuccess) { rc = IT_EHIP; break; }
       std::vector<int> still;
       for (int q : active)
         if (!prev[q].done) still.push_back(q);
@@ -1849,10 +1887,8 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
   if (rc == IT_OK && (hipMemcpyAsync(host, states, (size_t)ninst * sizeof(RunState), hipMemcpyDeviceToHost, stream) != hipSuccess ||
                       hipStreamSynchronize(stream) != hipSuccess))
     rc = IT_EHIP;
-  (void)hipEventDestroy(evs[0]);
-  (void)hipEventDestroy(evs[1]);
-  release_graph();
   if (rc) return rc;
+  drain.armed = false;  // the last read-back was waited for
   for (int q = 0; q < ninst; ++q) {
     fill_result(host[q], dts[q], ch[q].max_steps, issued, &out[q]);
     train_result(host[q], &ch[q], period_steps[q], &out[q]);
@@ -1860,8 +1896,16 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
   return IT_OK;
 }
 
-int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* exec, double* d_pos,
-               double* d_neg, void* d_workspace, size_t ws_bytes, void* stream_, double* h_trace) {
+int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_track* tracks,
+                   int32_t ninst, const it_exec* exec, void* d_workspace, size_t ws_bytes, void* stream_,
+                   it_result* out) {
+  return without_exceptions([&] {
+    return it_solve_batch_body(ch, track_offsets, tracks, ninst, exec, d_workspace, ws_bytes, stream_, out);
+  });
+}
+
+static int it_advance_body(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* exec, double* d_pos,
+                           double* d_neg, void* d_workspace, size_t ws_bytes, void* stream_, double* h_trace) {
   clear_stale_error();
   int rc = check_chamber(ch);
   if (rc) return rc;
@@ -1918,6 +1962,13 @@ int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* e
                            hipMemcpyDeviceToHost, stream));
   HIP_TRY(hipStreamSynchronize(stream));
   return IT_OK;
+}
+
+int it_advance(const it_chamber* ch, double dt, int64_t nsteps, const it_exec* exec, double* d_pos,
+               double* d_neg, void* d_workspace, size_t ws_bytes, void* stream_, double* h_trace) {
+  return without_exceptions([&] {
+    return it_advance_body(ch, dt, nsteps, exec, d_pos, d_neg, d_workspace, ws_bytes, stream_, h_trace);
+  });
 }
 
 }  // extern "C"
