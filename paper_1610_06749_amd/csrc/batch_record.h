@@ -36,7 +36,7 @@ __device__ inline void record_previous(const BatchInstance& bi, int parity, int 
   snapshot_state(p.state, &now);
   __syncthreads();
   if (now.done) {
-    if (threadIdx.x == 0 && threadIdx.y == 0) stop_after(p.state->stop, parity);
+    if (threadIdx.x == 0 && threadIdx.y == 0) p.state->done = kStopAll;
     return;
   }
   // the previous pass's tile count, which its own recording block stored
@@ -61,13 +61,13 @@ __device__ inline void record_previous(const BatchInstance& bi, int parity, int 
         st->pulses_counted = k + 1;
       }
     }
-    finalize_steps(st, &now, p.trace, totals, Te, step, p.cp, p.cn, p.dV, p.stop_tol, p.min_stop_step, inject,
-                   train ? now.pulse_q[0] : 0.0, train ? now.pulse_q[1] : 0.0);
-    if (!st->done && st->steps >= bi.max_steps) {
-      st->done = 1;
+    const int stopped = finalize_steps(st, &now, p.trace, totals, Te, step, p.cp, p.cn, p.dV, p.stop_tol,
+                                       p.min_stop_step, stop_after(parity), inject, train ? now.pulse_q[0] : 0.0,
+                                       train ? now.pulse_q[1] : 0.0);
+    if (!stopped && step + Te >= bi.max_steps) {
+      st->done = stop_after(parity);
       st->by_limit = 1;
     }
-    if (st->done) stop_after(st->stop, parity);
     st->rec_ntiles = bi.ntiles;  // this pass's tiles, for the next recording block
     if (train) {
       // the next pass computes steps c1 .. c1 + T - 1; a pulse at or past

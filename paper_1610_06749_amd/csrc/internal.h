@@ -56,11 +56,10 @@ struct RunState {
   double e_sums[3];         // electrons collected at anode, cathode; recombined
   double e_left;            // electrons in flight after the last electron step
   int64_t e_steps;          // electron-phase steps recorded
-  int32_t e_done;           // 1 once the electrons are collected
+  int32_t e_done;           // not 0 once the electrons are collected (see stop_flag.h)
   uint32_t dep_arrived;     // deposit tiles done (0 between deposits)
   int64_t steps;            // steps recorded so far
-  int32_t done;             // 1 once the stop criterion (or a non-finite tally) is met
-  StopFlags stop, e_stop;   // what the tile blocks of the one-step and the electron kernels look at
+  int32_t done;             // not 0 once the stop criterion (or a non-finite tally) is met (see stop_flag.h)
   int32_t flags;            // IT_FLAG_NONFINITE
   int32_t passes;           // stepping launches that ran (not skipped)
   int32_t by_limit;         // 1 if a batched run stopped the instance at max_steps
@@ -117,10 +116,10 @@ struct StepParams {
   // gsp = -mu+ dt q/eps0, gsn = +mu- dt q/eps0 (both 0 when off)
   double gsp, gsn;
   int absorbing;            // 1: absorbing lateral boundaries (zero beyond the cell), 0: periodic
+  int parity;               // of this launch (see stop_flag.h)
   int64_t step0;            // index of the step this launch computes
   int64_t min_stop_step;    // the stop criterion is tested only from this step on
   double* partials;         // [gridDim][kAcc * T]
-  int parity;               // of this launch (see StopFlags)
   RunState* state;
   double* trace;            // [max_steps][IT_TRACE_COLS]
   // when set, one extra block of the launch reduces the partials of the
@@ -184,7 +183,7 @@ struct Step3Params {
   double beta, dV, stop_tol;
   double* partials;         // [tiles' blocks][kAcc3]
   const double* prev_partials;  // when set, an extra block records the previous step from them
-  int parity;               // of this launch (see StopFlags)
+  int parity;               // of this launch (see stop_flag.h)
   RunState* state;
 };
 hipError_t launch_step3(const Step3Params& p, hipStream_t s);

@@ -35,7 +35,7 @@ void batch_step_kernel(const BatchInstance* __restrict__ inst, int ninst, int to
   if (L >= total_tiles) return;
   const int q = find_instance(inst, ninst, L);
   const StepParams& p = inst[q].sp[parity];
-  const bool done = launch_skips(p.state->stop, parity);
+  const bool done = launch_skips(p.state->done, parity);
   const int l = L - inst[q].tile_begin;
   TileCoord t = tile_of(l, p.tiles_x, p.tiles_y);
   t.valid = true;

@@ -23,10 +23,11 @@ __device__ void record_previous_pass(const StepParams& p) {
   snapshot_state(p.state, &now);
   reduce_partials<kBNT>(p.prev_partials, p.prev_nblocks, kAcc * p.prev_T, kAcc * p.prev_T, totals);
   if (threadIdx.x == 0 && threadIdx.y == 0) {
-    if (!now.done)
+    if (now.done)
+      p.state->done = kStopAll;
+    else
       finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
-                     p.min_stop_step);
-    if (p.state->done) stop_after(p.state->stop, p.parity);
+                     p.min_stop_step, stop_after(p.parity));
   }
 }
 

@@ -28,7 +28,7 @@ __device__ inline void record_step3(const Step3Params& p, const double* partials
   reduce_partials(partials, nblocks, kAcc3, kAcc3, tot);
   if (threadIdx.x != 0 || threadIdx.y != 0) return;
   if (now.e_done) {
-    stop_after(p.state->e_stop, p.parity);
+    p.state->e_done = kStopAll;
     return;
   }
   RunState& st = now;
@@ -48,13 +48,11 @@ __device__ inline void record_step3(const Step3Params& p, const double* partials
   for (int q = 0; q < kAcc3; ++q) finite = finite && isfinite(tot[q]);
   if (!finite) {
     st.flags |= IT_FLAG_NONFINITE;
-    st.e_done = 1;
-    st.done = 1;
-    stop_now(st.stop);  // no ion kernel is running
+    st.e_done = stop_after(p.parity);
+    st.done = kStopAll;  // no ion kernel is running
   } else if (tot[13] * dV <= p.stop_tol * st.released_e) {
-    st.e_done = 1;
+    st.e_done = stop_after(p.parity);
   }
-  if (st.e_done) stop_after(st.e_stop, p.parity);
   *p.state = st;
 }
 
@@ -72,7 +70,7 @@ __global__ __launch_bounds__(kNT3) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     record_step3(p, p.prev_partials, (int)gridDim.x - 1);
     return;
   }
-  if (launch_skips(p.state->e_stop, p.parity)) return;
+  if (launch_skips(p.state->e_done, p.parity)) return;
   __shared__ double sl[2][3][kTY3 + 2][kTX3 + 2];
   __shared__ double lds[(kNT3 / kWave) * kAcc3];
   double acc[kAcc3];

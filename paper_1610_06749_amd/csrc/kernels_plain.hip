@@ -27,7 +27,7 @@ namespace it {
 // boundary before this launch makes the previous partials visible; the
 // state it writes is read by the next launch.  Once it finds the run stopped,
 // this launch has computed a step past the stop, whose output goes to the field
-// pair not holding the stop step; the launches after it skip (see StopFlags).
+// pair not holding the stop step; the launches after it skip (see stop_flag.h).
 // Tiles of column pairs aim at 8 waves per CU, so they may use more
 // registers (at least 2 waves per SIMD instead of 4).
 template <int SY, bool SC, bool AB, int TX>
@@ -38,16 +38,17 @@ __global__ __launch_bounds__(kTX * SY) __attribute__((amdgpu_waves_per_eu(TX == 
     snapshot_state(p.state, &now);
     reduce_partials<kTX * SY>(p.prev_partials, p.prev_nblocks, kAcc * p.prev_T, kAcc * p.prev_T, totals);
     if (threadIdx.x == 0 && threadIdx.y == 0) {
-      if (!now.done)
+      if (now.done)
+        p.state->done = kStopAll;
+      else
         finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
-                       p.min_stop_step);
-      if (p.state->done) stop_after(p.state->stop, p.parity);
+                       p.min_stop_step, stop_after(p.parity));
     }
     return;
   }
   // set by an earlier launch: every block skips (read here, looked at once the
   // first planes are on their way)
-  const bool done = launch_skips(p.state->stop, p.parity);
+  const bool done = launch_skips(p.state->done, p.parity);
   const TileCoord t = decode_tile(p.tiles_x, p.tiles_y, p.ntiles, p.per_xcd);
   if constexpr (TX == 2 * kTX)
     pair_tile_step<SY, SC, AB>(p, t, done, p.partials + (size_t)blockIdx.x * kAcc);
@@ -65,10 +66,11 @@ __global__ __launch_bounds__(1024) void reduce_steps_kernel(StepParams p, int nb
   snapshot_state(p.state, &now);
   reduce_partials<1024>(p.partials, nblocks, kAcc * T, kAcc * T, totals);
   if (threadIdx.x == 0) {
-    if (!now.done)
-      finalize_steps(p.state, &now, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol,
-                     p.min_stop_step);
-    if (p.state->done) stop_now(p.state->stop);
+    if (now.done)
+      p.state->done = kStopAll;
+    else
+      finalize_steps(p.state, &now, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol, p.min_stop_step,
+                     kStopAll);
   }
 }
 

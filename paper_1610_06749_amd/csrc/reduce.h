@@ -152,10 +152,11 @@ __device__ inline void snapshot_state(const RunState* st, RunState* snap) {
 // the untouched fields through private memory); now: the state as it stands
 // (gst itself, or a copy in LDS).  inject_at >= 0: a pulse of
 // a batched pulse train released inj_pos and inj_neg ions before the step
-// step0 + inject_at, which are booked with that step.
-__device__ inline void finalize_steps(RunState* gst, const RunState* now, double* trace, const double* tot, int T,
+// step0 + inject_at, which are booked with that step.  stop: the stop flag to
+// leave if the run stops here; returns the flag left.
+__device__ inline int finalize_steps(RunState* gst, const RunState* now, double* trace, const double* tot, int T,
                                       int64_t step0, const Coef& cp, const Coef& cn, double dV,
-                                      double stop_tol, int64_t min_stop_step, int inject_at = -1,
+                                      double stop_tol, int64_t min_stop_step, int stop, int inject_at = -1,
                                       double inj_pos = 0.0, double inj_neg = 0.0) {
   double released = now->released, released_neg = now->released_neg;
   double pending = now->released_pending, pending_neg = now->released_pending_neg;
@@ -170,7 +171,7 @@ __device__ inline void finalize_steps(RunState* gst, const RunState* now, double
 #pragma unroll
   for (int q = 0; q < 4; ++q) last[q] = now->last[q];
   int64_t steps = now->steps;
-  int done = now->done, flags = now->flags;
+  int done = 0, flags = now->flags;
   const int64_t period_step = now->period_step;
   bool injected = false;
   for (int s = 0; s < T && !done; ++s) {
@@ -225,9 +226,9 @@ __device__ inline void finalize_steps(RunState* gst, const RunState* now, double
     steps = l + 1;
     if (!finite) {
       flags |= IT_FLAG_NONFINITE;
-      done = 1;
+      done = stop;
     } else if (l >= min_stop_step && rec[7] <= stop_tol * released && rec[8] <= stop_tol * released_neg) {
-      done = 1;
+      done = stop;
     }
   }
   gst->released_pending = pending;
@@ -250,6 +251,7 @@ __device__ inline void finalize_steps(RunState* gst, const RunState* now, double
   gst->done = done;
   gst->flags = flags;
   gst->passes = now->passes + 1;
+  return done;
 }
 
 // Tile coordinates: column tile (tx, ty) and z chunk.

@@ -21,15 +21,14 @@ using namespace it;
 // tile blocks records launch `close` before launch close + 1, which then has
 // no recording block.
 static int run(int last, int first_parity, int at, int waves, int close) {
-  StopFlags f = {{0, 0}};
-  bool done = false;
+  int f = 0;
   for (int l = 0; l < last + 8; ++l) {
     const int parity = (l + first_parity) & 1;
     int skipped = 0;
     for (int w = 0; w <= waves; ++w) {
       if (w == at && l > 0 && l - 1 != close) {
-        if (l - 1 == last) done = true;
-        if (done) stop_after(f, parity);
+        if (f) f = kStopAll;
+        else if (l - 1 == last) f = stop_after(parity);
       }
       if (w < waves) skipped += launch_skips(f, parity);
     }
@@ -38,8 +37,7 @@ static int run(int last, int first_parity, int at, int waves, int close) {
     const int until = close == last ? last : last + 1;
     if ((skipped == waves) != (l > until)) return 2;
     if (l == close) {
-      if (l == last) done = true;
-      if (done) stop_now(f);
+      if (f || l == last) f = kStopAll;
     }
   }
   return 0;
