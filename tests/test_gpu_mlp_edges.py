@@ -75,3 +75,10 @@ def test_an_answer_does_not_depend_on_the_call(gpu, precision):  # noqa: F811
             few = gpu.it_mlp_query(model, Q[first:first + n].contiguous(), 1e-3)
             for a, b in zip(few[:3], (mean, spread, fb)):
                 assert torch.equal(a, b[first:first + n]), (t_sigma, first, n)
+
+
+@pytest.mark.parametrize("n", [16, 61, 64, 65, 128, 129, 499, 500, 513, 628, 629, 1000])
+def test_fp32_gradient_at_group_edges(gpu, n):  # noqa: F811
+    """Samples around the groups in flight: 64 where a block adds the slices,
+    512 and then 128 where each block has its own."""
+    test_fp32_gradient_at_tile_edges(gpu, n)
