@@ -61,8 +61,8 @@ constexpr int kMinR = 3, kMaxR = 6;
 
 // Planes per chunk: the fewest chunks (each recomputes T planes of halo at
 // both ends) whose blocks still fill the machine in as few rounds of one
-// block per CU as possible.
-int zchunk_for(long cols, int nint, int T) {
+// block per CU as possible.  cost: iterations of a CU with the most blocks.
+int zchunk_for(long cols, int nint, int T, double* cost_out = nullptr) {
   constexpr long kCUs = 256;
   int best_zc = nint;
   double best = 1e30;
@@ -77,6 +77,7 @@ int zchunk_for(long cols, int nint, int T) {
       best_zc = zc;
     }
   }
+  if (cost_out) *cost_out = best;
   return best_zc;
 }
 
@@ -104,6 +105,13 @@ int blocked_supported(int T, int tile_y) {
   if (tile_y < 0 || tile_y % kBW) return 0;
   const int R = blocked_rows(T, tile_y);
   return R >= kMinR && R <= kMaxR ? 1 : 0;
+}
+
+double blocked_iterations(int nx, int ny, int nz, int T, int R) {
+  const int OX = kBX - 2 * T, OY = kBW * R - 2 * T;
+  double cost = 0.0;
+  (void)zchunk_for((long)((nx + OX - 1) / OX) * ((ny + OY - 1) / OY), nz - 1, T, &cost);
+  return cost;
 }
 
 void blocked_tiling(int nx, int ny, int nz, int T, int R, int* grid, int* per_xcd, int* tiles_x,
