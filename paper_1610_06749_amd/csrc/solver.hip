@@ -417,8 +417,10 @@ int auto_steps(const it_chamber* ch, const it_exec* ex, bool fields) {
 // Rows per thread of a single chamber's blocked passes.  Below
 // kBlockedTallNodes a launch is a few rounds of one block per CU, and three rows
 // are taken unless four save more iterations than the longer ones cost: an
-// iteration takes 1.2 times as long with four rows, 1.5 times with both the
-// space-charge term and absorbing sides.  us per step with three and four rows,
+// iteration takes 1.2 times as long with four rows, 1.6 times with both the
+// space-charge term and absorbing sides, whose four rows do not fit the
+// registers (256 x 256 x 200 nodes 62.2 and 69.6 us per step; the rule then holds
+// for every size).  us per step with three and four rows,
 // and one step per launch: 128 x 128 x 120 nodes 11.3, 14.2 and 16.9, 291 x 196
 // x 27 14.0, 16.8 and 18.3, 433 x 433 x 25 19.7, 24.5 and 41.4; but 530 x 530 x
 // 17 27.7, 19.2 and 48.0, 570 x 570 x 5 14.4, 9.9 and 18.6, 1224 x 1224 x 4 41.9,
@@ -426,8 +428,9 @@ int auto_steps(const it_chamber* ch, const it_exec* ex, bool fields) {
 // charge 28.5, 22.6 and 44.4.
 int run_rows(const it_chamber* ch, int T, int tile_y) {
   const int tall = blocked_rows(T, tile_y);
-  if (T != kBlockedT || tile_y != 0 || interior_nodes(ch) >= kBlockedTallNodes) return tall;
-  const double longer = ch->space_charge && ch->lateral_bc ? 1.5 : 1.2;
+  const bool both = ch->space_charge && ch->lateral_bc;
+  if (T != kBlockedT || tile_y != 0 || (interior_nodes(ch) >= kBlockedTallNodes && !both)) return tall;
+  const double longer = both ? 1.6 : 1.2;
   const double three = blocked_iterations(ch->nx, ch->ny, ch->nz, T, 3);
   return longer * blocked_iterations(ch->nx, ch->ny, ch->nz, T, tall) <= three * (1.0 + 1e-9) ? tall : 3;
 }

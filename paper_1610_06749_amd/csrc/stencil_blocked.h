@@ -203,8 +203,11 @@ __device__ __forceinline__ void blocked_tile_pass(const StepParams& p, const Til
   // T = 3 and 4, and T = 2 passes cut short in such runs), two buffers
   // alternate and each plane is loaded two iterations ahead, the march taking
   // two iterations per loop trip (1 % faster on the 512 x 512 x 256 grid, 2 %
-  // on the 96-chamber sweep); otherwise one buffer, one plane ahead.
-  constexpr bool kTwoBuffers = T * R <= 12 && R <= 4 && !(AB && T * R > 9);
+  // on the 96-chamber sweep); otherwise one buffer, one plane ahead.  The
+  // absorbing terms and, at T = 4, the space-charge tallies take the registers
+  // of the second one (T = 4 and three rows with space charge on 256 x 256 x 200
+  // nodes: 69.5 us per step with two and 35 registers spilled, 52.3 with one).
+  constexpr bool kTwoBuffers = T * R <= 12 && R <= 4 && !(AB && T * R > 9) && !(SC && T == 4);
   constexpr int kAhead = kTwoBuffers ? 2 : 1;
   double pa[R], na[R], pb[R], nb[R];
   auto load0 = [&](int K, double (&lp)[R], double (&ln)[R]) {
