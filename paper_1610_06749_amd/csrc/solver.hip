@@ -1472,7 +1472,7 @@ static int it_solve_body(const it_chamber* ch, const it_track* tracks, int64_t n
     HIP_TRY(hipMemcpyAsync(ws + L.off_tracks, dev.data(), dev.size() * sizeof(DepTrack),
                            hipMemcpyHostToDevice, stream));
 
-  // the deposit of step 0 (of nothing, if none is due then) writes the fields
+  // the deposit of step 0 writes the fields
   DepositParams dp = base_deposit(ch, dt, 1);
   dp.fresh = 1;
   dp.pos = (double*)(ws + L.off_field[0]);
@@ -1499,7 +1499,16 @@ static int it_solve_body(const it_chamber* ch, const it_track* tracks, int64_t n
     dp.attach = ch->attach_coeff;
     dp.pfree = free_fraction(ch->attach_coeff, ch->gap);
   }
-  HIP_TRY(launch_deposit(dp, stream));
+  if (fe || dp.npar || dp.ntilt || dp.uniform > 0.0) {
+    HIP_TRY(launch_deposit(dp, stream));
+  } else {
+    // nothing arrives with step 0: cleared instead (1000 x 1000 x 5 nodes, a call
+    // of two empty steps 265 us with a deposit of nothing, 130 so)
+    double* const pair0[2] = {dp.pos, dp.neg};
+    double* const pair1[2] = {dp.pos2, dp.neg2};
+    for (double* f : pair0) HIP_TRY(hipMemsetAsync(f, 0, L.field_elems * sizeof(double), stream));
+    HIP_TRY(launch_zero_electrodes(pair1, pair1, (size_t)ch->nx * ch->ny, ch->nz, stream));
+  }
   int64_t e_steps = 0;
   if (fe) {  // the electron phase; the ion phase below starts from its end
     rc = electron_phase(ch, dt, ws, L, stream, hs.p, &e_steps);
