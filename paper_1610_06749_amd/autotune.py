@@ -10,8 +10,9 @@ fastest per voxel-step:
   (the stepping kernel plus its tally reduction) on a perturbed field of the
   chamber's shape;
 * batched sweeps (``tune_batch``): the tile shape and planes per tile of the
-  batched kernel and the passes per captured graph, each timed on the batch
-  itself with the step count capped.
+  batched kernel and the passes per graph (and, for narrow chambers, the
+  library's own choice), each timed on the batch itself with the step count
+  capped.
 
 Results are cached per (grid, device) in memory and, when a path is given,
 in a JSON file, so one tuning serves every later run of that shape.
@@ -31,10 +32,15 @@ PLAIN = [dict(kernel=B.IT_KERNEL_PLAIN, tile_y=8), dict(kernel=B.IT_KERNEL_PLAIN
          dict(kernel=B.IT_KERNEL_PLAIN, tile_x=32)]
 PAIR = [dict(kernel=B.IT_KERNEL_PLAIN, tile_x=128)]  # tiles of column pairs: grids with an even nx
 # the temporally blocked kernel at each depth with its default rows per
-# thread, and the next larger tile that still fits the registers
+# thread, and the other tiles that fit the registers (at three steps per pass
+# the default is three or four rows by the grid)
 BLOCKED = [dict(kernel=B.IT_KERNEL_BLOCKED, steps_per_pass=T) for T in (2, 3, 4)] + \
     [dict(kernel=B.IT_KERNEL_BLOCKED, steps_per_pass=2, tile_y=40),
-     dict(kernel=B.IT_KERNEL_BLOCKED, steps_per_pass=3, tile_y=24)]
+     dict(kernel=B.IT_KERNEL_BLOCKED, steps_per_pass=3, tile_y=24),
+     dict(kernel=B.IT_KERNEL_BLOCKED, steps_per_pass=3, tile_y=32)]
+# the widest cross-section that the library's choice for a batch may give a
+# single block
+NARROW_NODES = 2048
 
 _memo: dict = {}
 
@@ -157,9 +163,19 @@ def batch_candidates(rows=(8,), graph_passes=(32,), z_chunks=(16,), narrow=False
     return out
 
 
+def library_candidates(chs, graph_passes=(32,)):
+    """The library's own choice, which no explicit one names where every
+    chamber is narrow, periodic and without space charge (a block per whole
+    cross-section then; as fast as twice a blocked pass)."""
+    narrow = all(c["nx"] * c["ny"] <= NARROW_NODES and not c.get("lateral_bc", 0) and not c.get("space_charge", 0)
+                 for c in chs)
+    return [dict(kernel=B.IT_KERNEL_AUTO, check_every=g) for g in graph_passes] if narrow else []
+
+
 def tune_batch(chs, trs, steps=96, candidates=None, cache=None, verbose=False, **kw):
     """Best ``exec`` for it_solve_batch on these chambers among
-    ``candidates`` (default: batch_candidates(**kw)), each timed on the batch
+    ``candidates`` (default: batch_candidates(**kw) and, for narrow chambers,
+    library_candidates), each timed on the batch
     with every instance's step count capped at ``steps``; a choice the
     batch does not support (IT_ENOTSUP, e.g. blocked passes for a train
     whose period is shorter than a pass) is skipped.  Cached per grids and
@@ -176,7 +192,10 @@ def tune_batch(chs, trs, steps=96, candidates=None, cache=None, verbose=False, *
     capped = [dict(c, max_steps=steps) for c in chs]
     vs = sum(c["nx"] * c["ny"] * (c["nz"] - 1) for c in chs) * steps
     timings = []
-    cands = candidates if candidates is not None else batch_candidates(**kw)
+    if candidates is not None:
+        cands = candidates
+    else:
+        cands = batch_candidates(**kw) + library_candidates(chs, kw.get("blocked_graph", (32,)))
     for ex in cands:
         try:
             B.it_solve_batch(capped, trs, exec=ex)  # warm-up
