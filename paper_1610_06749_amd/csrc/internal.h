@@ -234,3 +234,10 @@ hipError_t batch_pass_node(hipGraph_t graph, hipGraphExec_t exec, hipGraphNode_t
                            bool pu, int parity, int T, int R, int section_threads, bool crowded);
 
 }  // namespace it
+
+// Host only, for the tests: which passes it_solve_batch takes while the chambers
+// set[0..n) of the batch run.  form: rows per thread of the section passes (0:
+// none are taken), threads of a block, whether it is the form for many blocks
+// per CU, planes per chunk.
+extern "C" int it_batch_form(const it_chamber* ch, const int64_t* track_offsets, const it_track* tracks,
+                             int32_t ninst, const it_exec* exec, const int32_t* set, int32_t n, int32_t form[4]);

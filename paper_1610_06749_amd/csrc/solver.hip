@@ -1094,6 +1094,36 @@ Section batch_section_shape(const it_chamber* ch, int ninst, const int64_t* peri
   return best;
 }
 
+// Every instance's time step and a train's steps per period; T, the steps per
+// pass, becomes one where a period is shorter than a pass.
+int batch_times(const it_chamber* ch, const int64_t* track_offsets, const it_track* tracks, int ninst,
+                const it_exec* exec, int* T, std::vector<double>& dts, std::vector<int64_t>& period_steps) {
+  dts.resize(ninst);
+  period_steps.resize(ninst);
+  bool short_period = false;
+  for (int q = 0; q < ninst; ++q) {
+    const int64_t n = track_offsets[q + 1] - track_offsets[q];
+    const it_track* tq = n ? tracks + track_offsets[q] : nullptr;
+    const int rc = compute_dt(&ch[q], tq, n, &dts[q], &period_steps[q]);
+    if (rc) return rc;
+    for (int64_t k = 0; k < n; ++k)
+      if (deposit_step(tq[k].t_s, dts[q]) != 0) return IT_ENOTSUP;  // one pulse (or a train of it) per instance
+    short_period = short_period || (ch[q].n_pulses >= 2 && period_steps[q] < *T);
+  }
+  if (short_period) {
+    if (requested_steps(exec) > 0) return IT_ENOTSUP;
+    *T = 1;
+  }
+  return IT_OK;
+}
+
+// Section passes are taken where T, the steps per pass found so far, is the
+// library's choice, in the blocked passes' workspace.
+Section batch_section(const it_chamber* ch, int ninst, const it_exec* exec, int T, const int64_t* period_steps) {
+  if (T != kBlockedT || requested_steps(exec) != 0) return Section{};
+  return batch_section_shape(ch, ninst, period_steps);
+}
+
 // Section tiles of one chamber in chunks of zc planes.
 Tiling section_tiling(const it_chamber& c, int zc) {
   Tiling t;
@@ -1632,28 +1662,15 @@ static int it_solve_batch_body(const it_chamber* ch, const int64_t* track_offset
   // every instance's time step (and a train's steps per period) before any
   // device work: a pass of T steps takes at most one pulse, so a train with
   // a shorter period needs one step per pass
-  std::vector<double> dts(ninst);
-  std::vector<int64_t> period_steps(ninst);
-  bool short_period = false;
-  for (int q = 0; q < ninst; ++q) {
-    const int64_t n = track_offsets[q + 1] - track_offsets[q];
-    const it_track* tq = n ? tracks + track_offsets[q] : nullptr;
-    rc = compute_dt(&ch[q], tq, n, &dts[q], &period_steps[q]);
-    if (rc) return rc;
-    for (int64_t k = 0; k < n; ++k)
-      if (deposit_step(tq[k].t_s, dts[q]) != 0) return IT_ENOTSUP;  // one pulse (or a train of it) per instance
-    short_period = short_period || (ch[q].n_pulses >= 2 && period_steps[q] < T);
-  }
-  if (short_period) {
-    if (requested_steps(exec) > 0) return IT_ENOTSUP;
-    T = 1;
-  }
+  std::vector<double> dts;
+  std::vector<int64_t> period_steps;
+  rc = batch_times(ch, track_offsets, tracks, ninst, exec, &T, dts, period_steps);
+  if (rc) return rc;
   int R = T > 1 ? blocked_rows(T, exec ? exec->tile_y : 0) : 0;
   const int tile_x = exec_tile_x(exec, ch, ninst, false);
   const BatchLayout B = make_batch_layout(ch, track_offsets, ninst, rows, exec, tile_x, T, R);
   if (!d_workspace || ws_bytes < B.total) return IT_EWORKSPACE;
-  Section sec;  // section passes instead of blocked ones, in the same workspace
-  if (T == kBlockedT && requested_steps(exec) == 0) sec = batch_section_shape(ch, ninst, period_steps.data());
+  Section sec = batch_section(ch, ninst, exec, T, period_steps.data());
   if (sec.R) {
     T = kSectionT;
     R = sec.R;
@@ -1928,6 +1945,27 @@ int it_solve_batch(const it_chamber* ch, const int64_t* track_offsets, const it_
                    it_result* out) {
   return without_exceptions([&] {
     return it_solve_batch_body(ch, track_offsets, tracks, ninst, exec, d_workspace, ws_bytes, stream_, out);
+  });
+}
+
+int it_batch_form(const it_chamber* ch, const int64_t* track_offsets, const it_track* tracks, int32_t ninst,
+                  const it_exec* exec, const int32_t* set, int32_t n, int32_t form[4]) {
+  return without_exceptions([&]() -> int {
+    int rc = check_batch(ch, track_offsets, tracks, ninst);
+    if (rc) return rc;
+    int T = batch_steps(ch, ninst, exec);
+    rc = check_batch_steps(ch, ninst, exec, T);
+    if (rc) return rc;
+    std::vector<double> dts;
+    std::vector<int64_t> period_steps;
+    rc = batch_times(ch, track_offsets, tracks, ninst, exec, &T, dts, period_steps);
+    if (rc) return rc;
+    Section sec = batch_section(ch, ninst, exec, T, period_steps.data());
+    form[0] = sec.R;
+    form[1] = sec.threads;
+    form[3] = sec.R ? section_retile_z(ch, set, n, &sec) : 0;
+    form[2] = sec.crowded ? 1 : 0;
+    return IT_OK;
   });
 }
 
