@@ -6,10 +6,11 @@
 // the single-chamber kernel.  The same launch has one more block per
 // instance: it reduces that instance's partial tallies of the previous pass
 // (the partials alternate between two buffers) and records its step and stop
-// decision while the tile blocks compute the next step.  Blocks that read the
-// stop flag while it is being set only decide whether to compute one step
-// past the stop, which no result reads.  Kernel boundaries order the passes;
-// the host captures a chain of passes in a HIP graph and replays it until
+// decision while the tile blocks compute the next step.  The waves of a
+// block decide alike whether their instance has stopped (stop_flag.h; the passes
+// of several steps read the flag once per block); the pass in which the stop is
+// found is one past it, which no result reads.  Kernel boundaries order the passes;
+// the host makes a HIP graph of a chain of passes and replays it until
 // every instance has stopped.
 #include "batch_record.h"
 #include "stencil_blocked.h"

@@ -55,8 +55,12 @@ template <int R, bool CROWDED>
 const void* section_threads(int threads, bool pu) {
   if (threads <= 192) return section_ptr<R, 192, CROWDED>(pu);
   if (threads <= 256) return section_ptr<R, 256, CROWDED>(pu);
-  if (threads <= 384) return section_ptr<R, 384, CROWDED>(pu);
-  return section_ptr<R, 512, CROWDED>(pu);
+  if constexpr (CROWDED) {
+    return nullptr;  // a larger block has the CU to itself in either form
+  } else {
+    if (threads <= 384) return section_ptr<R, 384, false>(pu);
+    return section_ptr<R, 512, false>(pu);
+  }
 }
 
 }  // namespace

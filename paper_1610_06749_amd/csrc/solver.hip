@@ -1047,10 +1047,11 @@ static_assert(kSectionT == kBlockedT && kSectionMinZ >= kBlockedT, "partial slot
 // latency of an iteration, in issue times of one block's iteration
 constexpr double kSectionLatency = 1.5, kSectionLatencyCrowded = 2.0;
 
-// Blocks of w waves that share a CU with `slots` waves per SIMD (measured with
-// kernels of 160 registers: a block whose waves do not fill the SIMDs evenly
-// shares its CU with none, but for three waves, of which four blocks fit three
-// slots).
+// Blocks of w waves that share a CU with `slots` waves per SIMD: three in the
+// crowded form (126 to 168 registers), two in the other (up to 254).  Measured on
+// 24 x 24 sections with 160 registers: a block whose waves do not fill the SIMDs
+// evenly shares its CU with none, but for three waves, of which four blocks fit
+// three slots.
 int section_resident(int w, int slots) {
   if (w <= 2) return 4 * slots / w;
   if (w == 3) return slots >= 3 ? 4 : 2;
@@ -1154,7 +1155,7 @@ int section_retile_z(const it_chamber* ch, const int* set, int n, Section* s) {
       blocks += (planes + z - 1) / z;
     }
     const long per_cu = (blocks + kCUs - 1) / kCUs;
-    for (int crowded = 0; crowded <= (s->R <= 3 ? 1 : 0); ++crowded) {
+    for (int crowded = 0; crowded <= (s->R <= 3 && s->threads <= 256 ? 1 : 0); ++crowded) {
       const long resident = section_resident(waves, crowded ? 3 : 2), rounds = (per_cu + resident - 1) / resident;
       const double latency = crowded ? kSectionLatencyCrowded : kSectionLatency;
       const double cost = (z + 2.0 * kSectionT) * (latency * rounds + per_cu);
