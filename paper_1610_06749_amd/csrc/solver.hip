@@ -1064,8 +1064,8 @@ int section_resident(int w, int slots) {
 // times the share of lanes that hold a node.  Not where most lanes would idle
 // (a chamber among much narrower ones), and a period of a pulse train has to
 // be kSectionT steps or more: the blocked pass then.  On MI355X, 192 chambers
-// of 24 x 24 nodes and up to 300 planes take 37 us per step while all run
-// (blocked pass: 103).
+// of 24 x 24 nodes and up to 300 planes take 45 us per step while all run
+// (blocked pass: 107).
 Section batch_section_shape(const it_chamber* ch, int ninst, const int64_t* period_steps) {
   Section best;
   double best_score = 0.0;

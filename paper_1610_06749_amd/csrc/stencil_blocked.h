@@ -32,9 +32,12 @@
 // Against per-row branches, global addresses in vector registers and edge rows
 // of one species per access: 184.8 us instead of 189 per step on the
 // 512 x 512 x 256 grid, 39.7 instead of 40.2 on 256 x 256 x 200 (T = 3, R = 4).
-// What bounds the pass is FP64 issue (23 FP64 instructions and 8 lane shifts per
-// node, level and both species, about 1.5 of them per owned node with the rims)
-// at 75 % of the issue slots when nothing waits on HBM, and HBM beside it.
+// What bounds the pass is latency at two waves per SIMD: counters give VALU
+// issue in 0.53 of the slots (23 FP64 instructions and 8 lane shifts per node,
+// level and both species, 1.44 nodes computed per owned one on 512 x 512 x 256)
+// and 0.58 of the HBM peak in traffic.  Without its loads and stores of planes it
+// still took 156 of 185 us per step, so most of the rest is the chain of the
+// levels, their LDS exchange and the barrier per plane, not HBM.
 //
 // The per-step tallies (the same quantities as the one-step kernel, one
 // record per level) are taken on owned columns and on the block's own chunk
