@@ -33,9 +33,9 @@
 // of one species per access: 184.8 us instead of 189 per step on the
 // 512 x 512 x 256 grid, 39.7 instead of 40.2 on 256 x 256 x 200 (T = 3, R = 4).
 // What bounds the pass is latency at two waves per SIMD: counters give VALU
-// issue in 0.53 of the slots (23 FP64 instructions and 8 lane shifts per node,
+// issue in 0.54 of the slots (23 FP64 instructions and 8 lane shifts per node,
 // level and both species, 1.44 nodes computed per owned one on 512 x 512 x 256)
-// and 0.58 of the HBM peak in traffic.  Without its loads and stores of planes it
+// and 0.57 of the HBM peak in traffic.  Without its loads and stores of planes it
 // still took 156 of 185 us per step, so most of the rest is the chain of the
 // levels, their LDS exchange and the barrier per plane, not HBM.
 //
