@@ -62,7 +62,7 @@ __device__ inline void record_previous(const BatchInstance& bi, int parity, int 
       }
     }
     const int stopped = finalize_steps(st, &now, p.trace, totals, Te, step, p.cp, p.cn, p.dV, p.stop_tol,
-                                       p.min_stop_step, stop_after(parity), inject, train ? now.pulse_q[0] : 0.0,
+                                       p.min_stop_step, inject, train ? now.pulse_q[0] : 0.0,
                                        train ? now.pulse_q[1] : 0.0);
     if (!stopped && step + Te >= bi.max_steps) {
       st->done = stop_after(parity);

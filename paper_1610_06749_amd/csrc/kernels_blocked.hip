@@ -22,13 +22,9 @@ __device__ void record_previous_pass(const StepParams& p) {
   __shared__ double totals[kAcc * kMaxT];
   snapshot_state(p.state, &now);
   reduce_partials<kBNT>(p.prev_partials, p.prev_nblocks, kAcc * p.prev_T, kAcc * p.prev_T, totals);
-  if (threadIdx.x == 0 && threadIdx.y == 0) {
-    if (now.done)
-      p.state->done = kStopAll;
-    else
-      finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
-                     p.min_stop_step, stop_after(p.parity));
-  }
+  if (!now.done && threadIdx.x == 0 && threadIdx.y == 0)
+    finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
+                   p.min_stop_step);
 }
 
 // SC: with the space-charge term (two more tallies per level); AB: absorbing
@@ -41,11 +37,17 @@ __global__ __launch_bounds__(kBNT) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
   }
   // The extra block of this launch may set the stop flag while the others
   // start: one thread reads it for the whole block, so that every wave takes
-  // the same branch (the waves meet at barriers below).
+  // the same branch (the waves meet at barriers below).  The first block passes
+  // a stop on to launches of both parities (as a branch of the recording block
+  // it changed the schedule of the passes, which took 2 % longer with space
+  // charge and absorbing sides).
   __shared__ int stopped;
   if (threadIdx.x == 0 && threadIdx.y == 0) stopped = p.state->done;
   __syncthreads();
-  if (stopped) return;
+  if (stopped) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && threadIdx.y == 0) p.state->done = kStopAll;
+    return;
+  }
   const int L = blocked_tile_index(blockIdx.x, p.per_xcd);
   TileCoord tc = tile_of(L < p.ntiles ? L : 0, p.tiles_x, p.tiles_y);
   tc.valid = L < p.ntiles;

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kTX * SY) __attribute__((amdgpu_waves_per_eu(TX == 
         p.state->done = kStopAll;
       else
         finalize_steps(p.state, &now, p.trace, totals, p.prev_T, p.prev_step, p.cp, p.cn, p.dV, p.stop_tol,
-                       p.min_stop_step, stop_after(p.parity));
+                       p.min_stop_step);
     }
     return;
   }
@@ -69,8 +69,7 @@ __global__ __launch_bounds__(1024) void reduce_steps_kernel(StepParams p, int nb
     if (now.done)
       p.state->done = kStopAll;
     else
-      finalize_steps(p.state, &now, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol, p.min_stop_step,
-                     kStopAll);
+      finalize_steps<true>(p.state, &now, p.trace, totals, T, p.step0, p.cp, p.cn, p.dV, p.stop_tol, p.min_stop_step);
   }
 }
 

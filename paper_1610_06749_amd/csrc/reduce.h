@@ -152,11 +152,13 @@ __device__ inline void snapshot_state(const RunState* st, RunState* snap) {
 // the untouched fields through private memory); now: the state as it stands
 // (gst itself, or a copy in LDS).  inject_at >= 0: a pulse of
 // a batched pulse train released inj_pos and inj_neg ions before the step
-// step0 + inject_at, which are booked with that step.  stop: the stop flag to
-// leave if the run stops here; returns the flag left.
+// step0 + inject_at, which are booked with that step.  Returns the stop flag left
+// (ALONE: by a launch without tile blocks): the launch's parity is that of the
+// launches recorded so far plus one, as it records the launch before it.
+template <bool ALONE = false>
 __device__ inline int finalize_steps(RunState* gst, const RunState* now, double* trace, const double* tot, int T,
                                       int64_t step0, const Coef& cp, const Coef& cn, double dV,
-                                      double stop_tol, int64_t min_stop_step, int stop, int inject_at = -1,
+                                      double stop_tol, int64_t min_stop_step, int inject_at = -1,
                                       double inj_pos = 0.0, double inj_neg = 0.0) {
   double released = now->released, released_neg = now->released_neg;
   double pending = now->released_pending, pending_neg = now->released_pending_neg;
@@ -171,6 +173,7 @@ __device__ inline int finalize_steps(RunState* gst, const RunState* now, double*
 #pragma unroll
   for (int q = 0; q < 4; ++q) last[q] = now->last[q];
   int64_t steps = now->steps;
+  const int stop = ALONE ? kStopAll : stop_after((now->passes + 1) & 1);
   int done = 0, flags = now->flags;
   const int64_t period_step = now->period_step;
   bool injected = false;
