@@ -30,6 +30,7 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr int kBlockedT = 3;                // steps per pass of the blocked kernel when none is given
 constexpr double kBlockedMinNodes = 1.2e6;  // interior nodes from which the library chooses it
+constexpr int kThinPlanes = 8;              // see run_rows
 constexpr double kBlockedTallNodes = 5.0e6;  // and from which its tiles always have four rows per thread
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -394,7 +395,7 @@ int requested_steps(const it_exec* ex) {
 // 181 x 134 x 97 21.9 and 12.9, 40 x 300 x 200 24.0 and 13.9, 200 x 200 x 99
 // 32.3 and 15.7.  The number of planes does not enter: with the rows of
 // run_rows, a hundred grids of 1 to 260 planes between 1.2e6 and 5e6 nodes took
-// at most 5 % longer than one step per launch, most of them half.  Not when the caller
+// at most 5 % longer than one step per launch, most of them half as long.  Not when the caller
 // sets a one-step tile option, and not when the final fields are asked for and
 // the collection criterion may end the run (stop_tol > 0): a blocked pass that
 // contains the last step still computes the pass's later steps, so its fields
@@ -417,20 +418,21 @@ int auto_steps(const it_chamber* ch, const it_exec* ex, bool fields) {
 // Rows per thread of a single chamber's blocked passes.  Below
 // kBlockedTallNodes a launch is a few rounds of one block per CU, and three rows
 // are taken unless four save more iterations than the longer ones cost: an
-// iteration takes 1.2 times as long with four rows, 1.6 times with both the
+// iteration takes 1.27 times as long with four rows (1.15 times where the gap is
+// a few planes, most of which a level skips), 1.6 times with both the
 // space-charge term and absorbing sides, whose four rows do not fit the
 // registers (256 x 256 x 200 nodes 62.2 and 69.6 us per step; the rule then holds
-// for every size).  us per step with three and four rows,
-// and one step per launch: 128 x 128 x 120 nodes 11.3, 14.2 and 16.9, 291 x 196
-// x 27 14.0, 16.8 and 18.3, 433 x 433 x 25 19.7, 24.5 and 41.4; but 530 x 530 x
-// 17 27.7, 19.2 and 48.0, 570 x 570 x 5 14.4, 9.9 and 18.6, 1224 x 1224 x 4 41.9,
-// 37.5 and 41.4, 2121 x 2121 x 2 114, 87 and 135, 962 x 141 x 34 with space
-// charge 28.5, 22.6 and 44.4.
+// for every size).  us per step with three and four rows, and one step per
+// launch: 128 x 128 x 120 nodes 11.3, 14.2 and 16.9, 291 x 196 x 27 14.0, 16.8 and
+// 18.3, 433 x 433 x 25 19.7, 24.5 and 41.4, 190 x 180 x 99 16.4, 17.0 and 34.4 (with
+// absorbing sides 17.3, 18.7 and 35.0); but 530 x 530 x 17 27.7, 19.2 and 48.0,
+// 570 x 570 x 5 14.4, 9.9 and 18.6, 1224 x 1224 x 4 41.9, 37.5 and 41.4, 2121 x
+// 2121 x 2 114, 87 and 135, 962 x 141 x 34 with space charge 28.5, 22.6 and 44.4.
 int run_rows(const it_chamber* ch, int T, int tile_y) {
   const int tall = blocked_rows(T, tile_y);
   const bool both = ch->space_charge && ch->lateral_bc;
   if (T != kBlockedT || tile_y != 0 || (interior_nodes(ch) >= kBlockedTallNodes && !both)) return tall;
-  const double longer = both ? 1.6 : 1.2;
+  const double longer = both ? 1.6 : ch->nz - 1 <= kThinPlanes ? 1.15 : 1.27;
   const double three = blocked_iterations(ch->nx, ch->ny, ch->nz, T, 3);
   return longer * blocked_iterations(ch->nx, ch->ny, ch->nz, T, tall) <= three * (1.0 + 1e-9) ? tall : 3;
 }
