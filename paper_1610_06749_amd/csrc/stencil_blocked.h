@@ -35,7 +35,7 @@
 // What bounds the pass is latency at two waves per SIMD: counters give VALU
 // issue in 0.54 of the slots (23 FP64 instructions and 8 lane shifts per node,
 // level and both species, 1.44 nodes computed per owned one on 512 x 512 x 256)
-// and 0.57 of the HBM peak in traffic.  Without its loads and stores of planes it
+// and 0.58 of the HBM peak in traffic.  Without its loads and stores of planes it
 // still took 156 of 185 us per step, so most of the rest is the chain of the
 // levels, their LDS exchange and the barrier per plane, not HBM.
 //
